@@ -44,7 +44,8 @@ bool dtype_of(vtrace_dtype d, LogitsType* lt) {
 }
 
 // Kernel choice: the time-parallel kernel for short unrolls of small batches,
-// the tiled kernel where it applies, else the generic one.  VTRACE_KERNEL
+// the tiled kernel where it applies, the row-split kernel for more actions,
+// else the generic one.  VTRACE_KERNEL
 // (lane_serial, tiled, tiled_single, tiled_short, tiled_short_single or wide)
 // forces a kernel where it applies, to cross-check them: tiled_single is the
 // tiled kernel with one workgroup per tile, never the multi-tile walk;
@@ -194,6 +195,8 @@ vtrace_status launch(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s)
   else if (tiled)
     e = vtrace::launch_tiled(a, lt, mode, s, &nwg, k != Kernel::TiledSingle && k != Kernel::TiledShortSingle,
                              k != Kernel::TiledShort && k != Kernel::TiledShortSingle);
+  else if (vtrace::rows_supported(a, lt))
+    e = vtrace::launch_rows(a, lt, mode, s, &nwg);
   else
     e = vtrace::launch_lane_serial(a, lt, mode, s, &nwg);
   return e == hipSuccess ? VTRACE_OK : VTRACE_ERR_HIP;

@@ -81,6 +81,10 @@ hipError_t launch_tiled_a10_14(const StepArgs& a, LogitsType lt, Mode mode, hipS
                                int64_t* num_workgroups, bool allow_multi);
 hipError_t launch_tiled_a15_20(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s,
                                int64_t* num_workgroups, bool allow_multi);
+// The row-split kernel covers kTiledMaxActions < A <= kRowsMaxActions.
+constexpr int64_t kRowsMaxActions = 256;
+bool rows_supported(const StepArgs& a, LogitsType lt);
+hipError_t launch_rows(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s, int64_t* num_workgroups);
 bool wide_supported(const StepArgs& a, LogitsType lt);
 hipError_t launch_wide(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s,
                        int64_t* num_workgroups);

@@ -86,6 +86,31 @@ __device__ __forceinline__ bool wave_rows_finite(const float (&v)[A_], float m) 
   return __all(__builtin_isfinite(mn) && __builtin_isfinite(m)) != 0;
 }
 
+// The rest of a target row's precise statistics (all of RowStats but the
+// ratio) from its maximum mz, its logit at the taken action za, the sums
+// sz = sum_j e_j and ed = sum_j e_j (z_j - m_z) log2 e, and ea = e_a.
+__device__ __forceinline__ void finish_target_stats(RowStats& st, float mz, float za, double sz, double ed,
+                                                    double ea) {
+  st.mz = mz;
+  if (!__builtin_isfinite(mz)) sz = NAN;
+  const double dza = static_cast<double>(za) - static_cast<double>(mz);  // exact
+  // 1/s from the hardware reciprocal and two Newton steps.
+  double inv = __builtin_amdgcn_rcp(sz);
+  inv = fma(inv, fma(-sz, inv, 1.0), inv);
+  inv = fma(inv, fma(-sz, inv, 1.0), inv);
+  const double log_sz = log_sum_f64(sz);
+  st.log_pa = dza - log_sz;
+  st.inv_s = static_cast<float>(inv);
+  st.log_s = static_cast<float>(log_sz);
+  st.one_minus_pa = static_cast<float>((sz - ea) * inv);
+  st.e_a = static_cast<float>(ea);
+  st.H = static_cast<float>(fma(-ed * kLn2F64, inv, log_sz));
+  st.ratio = 0.0;
+  st.sum = sz;
+  st.inv = inv;
+  st.dza = dza;
+}
+
 template <int A_, typename In>
 __device__ __forceinline__ RowStats target_row_stats(const In* zr, int act_c, float* e, float* zo) {
   RowStats st;
@@ -96,7 +121,6 @@ __device__ __forceinline__ RowStats target_row_stats(const In* zr, int act_c, fl
 #pragma unroll
     for (int j = 0; j < A_; ++j) zo[j] = z[j];
   }
-  st.mz = mz;
   const double mzl = static_cast<double>(mz) * kLog2eF64;
   // The sums start from -0.0, the additive identity, which lets the compiler
   // drop the first addition.
@@ -120,23 +144,7 @@ __device__ __forceinline__ RowStats target_row_stats(const In* zr, int act_c, fl
     terms(std::false_type{});
   else
     terms(std::true_type{});
-  if (!__builtin_isfinite(mz)) sz = NAN;
-  const double dza = static_cast<double>(za) - static_cast<double>(mz);  // exact
-  // 1/s from the hardware reciprocal and two Newton steps.
-  double inv = __builtin_amdgcn_rcp(sz);
-  inv = fma(inv, fma(-sz, inv, 1.0), inv);
-  inv = fma(inv, fma(-sz, inv, 1.0), inv);
-  const double log_sz = log_sum_f64(sz);
-  st.log_pa = dza - log_sz;
-  st.inv_s = static_cast<float>(inv);
-  st.log_s = static_cast<float>(log_sz);
-  st.one_minus_pa = static_cast<float>((sz - ea) * inv);
-  st.e_a = static_cast<float>(ea);
-  st.H = static_cast<float>(fma(-ed * kLn2F64, inv, log_sz));
-  st.ratio = 0.0;
-  st.sum = sz;
-  st.inv = inv;
-  st.dza = dza;
+  finish_target_stats(st, mz, za, sz, ed, ea);
   return st;
 }
 
