@@ -43,14 +43,14 @@ bool dtype_of(vtrace_dtype d, LogitsType* lt) {
   return false;
 }
 
-// Kernel choice: the time-parallel kernel for short unrolls of small batches,
-// the tiled kernel where it applies, the row-split kernel for more actions,
-// else the generic one.  VTRACE_KERNEL
-// (lane_serial, tiled, tiled_single, tiled_short, tiled_short_single or wide)
-// forces a kernel where it applies, to cross-check them: tiled_single is the
-// tiled kernel with one workgroup per tile, never the multi-tile walk;
-// tiled_short keeps its 16-step tiles, never the long-run tile shapes;
-// tiled_short_single both.
+// Kernel choice: the tiled kernel where it applies, the row-split kernel for
+// more actions, else the generic one.  VTRACE_KERNEL (lane_serial, tiled,
+// tiled_single, tiled_short, tiled_short_single or wide) forces a kernel or a
+// family of the tiled kernel's shapes where it applies, to cross-check them:
+// wide is the time-parallel shape, whose one chunk holds the whole unroll;
+// tiled the shapes that walk chunks shorter than the unroll; tiled_single the
+// same with one workgroup per tile, never the multi-tile walk; tiled_short the
+// 16-step tiles alone; tiled_short_single both.
 enum class Kernel { Auto, LaneSerial, Tiled, TiledSingle, TiledShort, TiledShortSingle, Wide };
 Kernel forced_kernel() {
   const char* k = std::getenv("VTRACE_KERNEL");
@@ -62,21 +62,6 @@ Kernel forced_kernel() {
   if (std::strcmp(k, "tiled_short_single") == 0) return Kernel::TiledShortSingle;
   if (std::strcmp(k, "wide") == 0) return Kernel::Wide;
   return Kernel::Auto;
-}
-
-// Where both apply, the time-parallel kernel wins while the tiled kernel's
-// serial walk over T / 16 chunks costs more than the time-parallel kernel's
-// uncoalesced row reads.  Measured on MI355X (cold, A = 9 and 18, T from 16
-// to 256, B from 8 to 2048, fp32 logits): batches of fewer than 16 lanes (less
-// than one lane tile) at every T; loss calls of more than one chunk and
-// targets-only calls of more than two, with B <= 512, or with B <= 1024 and
-// T <= 128 (for loss calls only with A = 18).  The DMLab- and Atari-shaped
-// batches (B = 32, T = 100 and 20) take it.
-bool prefer_wide(const StepArgs& a, Mode mode) {
-  if (a.B < 16) return true;
-  const bool loss = mode == Mode::LossGrad;
-  if (a.T <= (loss ? 16 : 32)) return false;
-  return a.B <= 512 || (a.B <= 1024 && a.T <= 128 && (!loss || a.A >= 18));
 }
 
 size_t workspace_bytes_for(int64_t B) {
@@ -186,15 +171,15 @@ vtrace_status launch(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s)
   int64_t nwg = 0;
   hipError_t e;
   const Kernel k = forced_kernel();
-  const bool wide = vtrace::wide_supported(a, lt);
-  const bool tiled = vtrace::tiled_supported(a, lt);
+  vtrace::TileRule rule;
+  rule.multi = k != Kernel::TiledSingle && k != Kernel::TiledShortSingle;
+  rule.shapes = k != Kernel::TiledShort && k != Kernel::TiledShortSingle;
+  rule.one_chunk = k != Kernel::Tiled && k != Kernel::TiledSingle;
+  rule.time_parallel = k == Kernel::Wide && a.T <= vtrace::kMaxChunkSteps;
   if (k == Kernel::LaneSerial)
     e = vtrace::launch_lane_serial(a, lt, mode, s, &nwg);
-  else if (wide && (k == Kernel::Wide || (k == Kernel::Auto && prefer_wide(a, mode))))
-    e = vtrace::launch_wide(a, lt, mode, s, &nwg);
-  else if (tiled)
-    e = vtrace::launch_tiled(a, lt, mode, s, &nwg, k != Kernel::TiledSingle && k != Kernel::TiledShortSingle,
-                             k != Kernel::TiledShort && k != Kernel::TiledShortSingle);
+  else if (vtrace::tiled_supported(a, lt))
+    e = vtrace::launch_tiled(a, lt, mode, s, &nwg, rule);
   else if (vtrace::rows_supported(a, lt))
     e = vtrace::launch_rows(a, lt, mode, s, &nwg);
   else

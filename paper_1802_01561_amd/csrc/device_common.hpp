@@ -181,28 +181,36 @@ constexpr int kWaitVmcnt0 = 0x0F70;
 // fence would in addition write back and invalidate the XCD's L2 for ordinary
 // accesses, which nothing here needs; in a short call those fences cost
 // several microseconds.
-template <int kThreads>
-__device__ void finish_losses(const StepArgs& a, double pg, double base, double ent,
-                              double* scratch) {
-  __shared__ int s_last;
-  block_sum3<kThreads>(pg, base, ent, scratch);
+//
+// The step is split in two for callers that have other stores to issue between
+// them: publish_losses (one thread) stores the workgroup's sums, finish_ticket
+// (every thread) waits, draws the ticket and finishes the totals.
+__device__ __forceinline__ void store_totals(const StepArgs& a, double pg, double base, double ent) {
+  a.losses[0] = static_cast<float>(pg + base + ent);
+  a.losses[1] = static_cast<float>(pg);
+  a.losses[2] = static_cast<float>(base);
+  a.losses[3] = static_cast<float>(ent);
+}
+
+__device__ __forceinline__ void publish_losses(const StepArgs& a, double pg, double base, double ent) {
   if (gridDim.x == 1) {
     // One workgroup: its sums are the totals (the same values the ticket path
     // would add to zero), without the round trips through memory.
-    if (threadIdx.x == 0) {
-      a.losses[0] = static_cast<float>(pg + base + ent);
-      a.losses[1] = static_cast<float>(pg);
-      a.losses[2] = static_cast<float>(base);
-      a.losses[3] = static_cast<float>(ent);
-    }
+    store_totals(a, pg, base, ent);
     return;
   }
+  double* p = a.partials + 3 * static_cast<size_t>(blockIdx.x);
+  __hip_atomic_store(p + 0, pg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(p + 1, base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(p + 2, ent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int kThreads>
+__device__ __forceinline__ void finish_ticket(const StepArgs& a, double* scratch) {
+  __shared__ int s_last;
+  if (gridDim.x == 1) return;
   if (threadIdx.x == 0) {
-    double* p = a.partials + 3 * static_cast<size_t>(blockIdx.x);
-    __hip_atomic_store(p + 0, pg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 1, base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(p + 2, ent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);  // keep the compiler from moving them past the wait
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);  // keep the compiler from moving the stores past the wait
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);  // the partial stores have completed
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     const unsigned prev = __hip_atomic_fetch_add(a.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -219,12 +227,17 @@ __device__ void finish_losses(const StepArgs& a, double pg, double base, double 
   }
   block_sum3<kThreads>(s0, s1, s2, scratch);
   if (threadIdx.x == 0) {
-    a.losses[0] = static_cast<float>(s0 + s1 + s2);
-    a.losses[1] = static_cast<float>(s0);
-    a.losses[2] = static_cast<float>(s1);
-    a.losses[3] = static_cast<float>(s2);
+    store_totals(a, s0, s1, s2);
     __hip_atomic_store(a.ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+}
+
+template <int kThreads>
+__device__ __forceinline__ void finish_losses(const StepArgs& a, double pg, double base, double ent,
+                                              double* scratch) {
+  block_sum3<kThreads>(pg, base, ent, scratch);
+  if (threadIdx.x == 0) publish_losses(a, pg, base, ent);
+  finish_ticket<kThreads>(a, scratch);
 }
 
 __device__ __forceinline__ void raise_error_flag(unsigned int* flag) {

@@ -49,8 +49,8 @@ constexpr size_t kWsHeaderBytes = 256;
 constexpr size_t kWsTicketOffset = 0;
 constexpr size_t kWsFlagOffset = 4;
 // Every loss kernel covers at least this many lanes per workgroup, so the
-// partials array is sized by ceil(B / kMinLanesPerWorkgroup).  (The
-// time-parallel kernel holds a single lane per workgroup for T > 128.)
+// partials array is sized by ceil(B / kMinLanesPerWorkgroup).  (Tiles of 256
+// steps and the row-split kernel hold a single lane per workgroup.)
 constexpr int64_t kMinLanesPerWorkgroup = 1;
 
 enum class LogitsType { F32, BF16 };
@@ -61,13 +61,20 @@ hipError_t launch_lane_serial(const StepArgs& a, LogitsType lt, Mode mode, hipSt
                               int64_t* num_workgroups);
 bool tiled_supported(const StepArgs& a, LogitsType lt);
 // The tiled kernel covers 2 <= A <= kTiledMaxActions (beyond, its per-thread
-// prefetch no longer fits the registers of two waves per SIMD).  allow_multi
-// false keeps one workgroup per tile (no multi-tile walk).
+// prefetch no longer fits the registers of two waves per SIMD) and batches whose
+// 16 time rows its 32-bit offsets reach.
 constexpr int64_t kTiledMaxActions = 20;
-// allow_long false keeps the 16-step tiles of 16 or 32 lanes (no long-run
-// tile shapes).
+// Which tile shapes a call may take.
+struct TileRule {
+  bool multi = true;      // the multi-tile walk
+  bool shapes = true;     // any shape; false keeps the 16-step tiles of 16 or 32 lanes
+  bool one_chunk = true;  // chunks as long as the unroll; false keeps those shorter than it
+  bool time_parallel = false;  // the shape whose one chunk holds the unroll, always
+};
 hipError_t launch_tiled(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s,
-                        int64_t* num_workgroups, bool allow_multi, bool allow_long);
+                        int64_t* num_workgroups, const TileRule& rule);
+// Whether TileRule::time_parallel applies (the unroll fits a chunk).
+constexpr int64_t kMaxChunkSteps = 256;
 // Long-run tile shapes for A = 9 and A = 18 (targets-only calls in the float32
 // ratio mode; loss calls by a rule of their own): true (with the launch
 // status in *err) when one applies and was launched.
@@ -75,19 +82,16 @@ bool launch_tiled_long_f32(const StepArgs& a, Mode mode, hipStream_t s, int64_t*
                            bool allow_multi, hipError_t* err);
 bool launch_tiled_long_bf16(const StepArgs& a, Mode mode, hipStream_t s, int64_t* num_workgroups,
                             bool allow_multi, hipError_t* err);
-hipError_t launch_tiled_a2_8(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s,
+hipError_t launch_tiled_a2_8(const StepArgs& a, LogitsType lt, int lanes, Mode mode, hipStream_t s,
                              int64_t* num_workgroups, bool allow_multi);
-hipError_t launch_tiled_a10_14(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s,
+hipError_t launch_tiled_a10_14(const StepArgs& a, LogitsType lt, int lanes, Mode mode, hipStream_t s,
                                int64_t* num_workgroups, bool allow_multi);
-hipError_t launch_tiled_a15_20(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s,
+hipError_t launch_tiled_a15_20(const StepArgs& a, LogitsType lt, int lanes, Mode mode, hipStream_t s,
                                int64_t* num_workgroups, bool allow_multi);
 // The row-split kernel covers kTiledMaxActions < A <= kRowsMaxActions.
 constexpr int64_t kRowsMaxActions = 256;
 bool rows_supported(const StepArgs& a, LogitsType lt);
 hipError_t launch_rows(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s, int64_t* num_workgroups);
-bool wide_supported(const StepArgs& a, LogitsType lt);
-hipError_t launch_wide(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s,
-                       int64_t* num_workgroups);
 hipError_t launch_gather(int64_t T, int64_t B, int64_t A, LogitsType lt, const void* target,
                          const void* behaviour, const int32_t* actions, void* gathered,
                          hipStream_t s);

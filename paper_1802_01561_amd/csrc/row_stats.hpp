@@ -1,5 +1,5 @@
 // Per-step row statistics of the target and behaviour logits, shared by the
-// tiled and time-parallel V-trace kernels.
+// tiled and row-split V-trace kernels.
 #pragma once
 
 #include <type_traits>

@@ -278,9 +278,10 @@ __global__ __launch_bounds__(kRowsThreads, K == 2 ? 3 : 2) void rows_kernel(Step
       auto next_step = [&](double x, double carry) {
         double n = dpp_f64<kRowShl1>(x);
         if constexpr (L == 64) {
-          if (s == 15) n = wave_read_f64<16>(x);
-          if (s == 31) n = wave_read_f64<32>(x);
-          if (s == 47) n = wave_read_f64<48>(x);
+          const double x16 = wave_read_f64<16>(x), x32 = wave_read_f64<32>(x), x48 = wave_read_f64<48>(x);
+          n = s == 15 ? x16 : n;
+          n = s == 31 ? x32 : n;
+          n = s == 47 ? x48 : n;
         }
         if (s == L - 1) n = carry;
         return n;

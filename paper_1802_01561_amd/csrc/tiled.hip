@@ -5,75 +5,111 @@
 
 namespace vtrace {
 
-bool tiled_supported(const StepArgs& a, LogitsType) { return a.A >= 2 && a.A <= kTiledMaxActions; }
+bool tiled_supported(const StepArgs& a, LogitsType) {
+  return a.A >= 2 && a.A <= kTiledMaxActions && rows_fit(a, kL);
+}
 
-// Lanes per workgroup: 16 (256 threads) for A = 9 keeps twice as many
-// workgroups in flight for mid-sized batches (a 4096-lane batch fills all 256
-// CUs), but once 32-lane tiles cover every CU, fp32 A = 9 takes 32 (1152-byte
-// runs, nine 128-byte lines, as for fp32 A = 18): measured at T = 1000, 503 ->
-// 436 us for 16384 lanes and 2.00 -> 1.71 ms for 65536, while 4096 lanes
-// slow from 133 to 199 us (half the CUs idle).  bf16 A = 9 measured slower
-// with 32 lanes at every size and keeps 16.  fp32 A = 18 uses 16 lanes (its
-// rows are already 1152 bytes).  bf16 A = 18 is the mirror image of fp32
-// A = 9: 32 lanes (1152-byte rows) once the tiles fill every CU twice, 16
-// below that (T = 1000: 4096 lanes 252 -> 167 us and 8192 lanes 297 -> 275 us
-// with 16; 16384 lanes 593 -> 558 us and 32768 lanes 1.23 -> 1.10 ms with 32),
-// and 32 when the whole batch is one tile (one workgroup, whose loss sums need
-// no cross-workgroup reduction).
-//
-// These are the shapes with 16-step chunks.  Batches of A = 9 or 18 that fill
-// the chip in whole generations take the long-run shapes of tiled_long_f32.hip
-// and tiled_long_bf16.hip first (32 to 128 lanes, chunks of 8 or 4 steps).
-constexpr int64_t kTwoRowMinT = 512;
+// Tiles of 256 threads: `lanes` lanes, 256 / lanes steps per chunk.
+constexpr int kTileThreads = 256;
+
+// Steps per chunk of the time-parallel shape: the power of two >= T, 16 to 256.
+int one_chunk_steps(int64_t T) {
+  int L = 16;
+  while (L < T && L < kMaxChunkSteps) L *= 2;
+  return L;
+}
+
+// Lanes per workgroup, 16 to 1, of the shapes that spread a small batch over
+// the chip: fewer lanes and longer chunks make more workgroups and fewer chunks
+// one after another, at shorter runs per time row.  The largest tile that gives
+// 7/8 of the CUs a workgroup; chunks no longer than the unroll needs.
+// Measured (loss call, fp32, calls in a HIP graph, us; 16 / 8 / 4 / 2 / 1 lanes):
+//   T = 1000, A = 18: B = 64 197 / 103 / 56 / 35 / 25, B = 512 204 / 110 / 65 /
+//   47 / 51, B = 2048 210 / 125 / 127 / 156 / 180;
+//   T = 100, A = 6: B = 100 16.5 / 12.1 / 8.9 / 7.6 / 8.3, B = 1021 17.4 / 13.7 /
+//   12.5 / 14.6 / 21.8, B = 2048 18.0 / 16.2 / 17.0 / 23.0 / 35.1;
+//   T = 20, A = 18: B = 512 11.6 / 9.0 / 9.7 / 11.5 / 15.1.
+int tile_lanes(const StepArgs& a, int cus, bool one_chunk) {
+  int min_lanes = kTileThreads / one_chunk_steps(a.T);
+  if (!one_chunk && a.T <= kMaxChunkSteps && min_lanes < 16) min_lanes *= 2;
+  auto tiles = [&](int lanes) { return (a.B + lanes - 1) / lanes; };
+  int lanes = 16;
+  while (lanes > 1 && (lanes > a.B || (lanes > min_lanes && tiles(lanes) * 8 < 7 * static_cast<int64_t>(cus))))
+    lanes /= 2;
+  // With short rows two chunks of the next larger tile cost no more than one of
+  // this on half the CUs (B = 1024, T = 50: A = 6 10.0 against 10.0, A = 9 11.0
+  // against 10.4 us; A = 18 13.2 against 12.1; T = 20, 8 to 16 lanes: B = 3000,
+  // A = 4 10.5 against 9.9, B = 2048, A = 9 9.8 against 10.5).
+  const int next_steps = kTileThreads / (2 * lanes);
+  if (lanes < 16 && a.A < (lanes == 8 ? 7 : 16) && a.T <= 2 * next_steps && a.T > next_steps &&
+      tiles(2 * lanes) * 2 >= cus)
+    lanes *= 2;
+  if (lanes == 16) {
+    // One 16-lane workgroup per CU against two of 8 lanes: the second wave per
+    // SIMD pays once the walk is long enough for the work of a row (B = 4096:
+    // T = 1000, A = 18 220 -> 202 us, T = 200, A = 6 31.2 -> 28.8, T = 100, A = 9
+    // 24.3 -> 23.4 and with bf16 logits and gradients 28.2 -> 25.5; T = 100,
+    // A = 6 20.3 against 20.8, T = 20, A = 6 11.6 against 13.4).
+    if (tiles(16) <= cus && a.T * a.A >= 900) return 8;
+    // A second generation of 16-lane workgroups that would leave half the chip
+    // idle runs faster as a third of 8 lanes, in long unrolls (T = 1000: B =
+    // 10000, A = 18 612 -> 555 us, B = 8200, A = 9 376 -> 343; T = 100: 70 against
+    // 70 and 49 against 50).
+    if (tiles(16) > 2 * cus && tiles(16) <= 3 * cus && a.T * a.A >= 9000) return 8;
+  }
+  return lanes;
+}
+
+// Lanes per workgroup of the 16-step tiles where 16 and 32 both fit.  fp32
+// A = 18 and other action counts: 16 (fp32 A = 18 rows are 1152 bytes).  bf16
+// A = 18: 32 (1152-byte rows) once the tiles fill every CU twice (T = 1000:
+// 16384 lanes 593 -> 558 us and 32768 lanes 1.23 -> 1.10 ms with 32, 8192 lanes
+// 275 against 297 us), and when the whole short batch is one such tile (one
+// workgroup, whose loss sums need no cross-workgroup reduction).  fp32 A = 9: 32
+// (1152-byte rows) once they give every CU two workgroups (T = 1000, 16000 lanes
+// 482 -> 462 us; 9000 lanes 396 against 441, T = 100 51 against 58).  bf16 A = 9
+// measured slower with 32 lanes at every size.
+bool wide_tiles(const StepArgs& a, LogitsType lt, int cus, bool short_batch) {
+  if (a.A == 18 && lt == LogitsType::BF16) return a.B >= 64 * static_cast<int64_t>(cus) || (short_batch && a.B == 32);
+  return a.A == 9 && lt == LogitsType::F32 && a.B >= 62 * static_cast<int64_t>(cus);
+}
 
 hipError_t launch_tiled(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t st,
-                        int64_t* num_workgroups, bool allow_multi, bool allow_long) {
-  if (allow_long && (a.A == 9 || a.A == 18)) {
-    hipError_t err = hipSuccess;
-    const bool launched = lt == LogitsType::F32
-                              ? launch_tiled_long_f32(a, mode, st, num_workgroups, allow_multi, &err)
-                              : launch_tiled_long_bf16(a, mode, st, num_workgroups, allow_multi, &err);
-    if (launched) return err;
-  }
-  // A = 18 batches whose 16-lane tiles give each CU at most one workgroup
-  // (B <= 16 x CUs: one wave per SIMD) take 32-step chunks for long unrolls:
-  // two waves per SIMD and half as many chunks one after another.  Measured
-  // (loss call, fp32 logits, event-timed medians): T = 512, B = 4096 0.147 ->
-  // 0.137 ms; T = 1000, B = 4096 0.267 -> 0.248 ms and B = 2048 0.228 ->
-  // 0.200 ms.  Not taken for A = 9 (T = 512-768: 2-6% slower) nor for
-  // shorter unrolls (T = 100-200: 2-8% slower; the 30-task batch 27.7 ->
-  // 29.8 us cold), where a 32-step chunk wastes more of the last one and the
-  // latency it hides is not what bounds the call.
-  if (allow_long && a.A == 18 && a.T >= kTwoRowMinT) {
-    const int cus = compute_units();
-    if (cus > 0 && a.B <= 16 * static_cast<int64_t>(cus)) {
-      if (lt == LogitsType::F32) return launch_shape<18, 16, float, 32>(a, mode, st, num_workgroups, allow_multi);
-      return launch_shape<18, 16, uint16_t, 32>(a, mode, st, num_workgroups, allow_multi);
-    }
-  }
-  if (lt == LogitsType::F32) {
-    if (a.A == 18) return launch_shape<18, 16, float>(a, mode, st, num_workgroups, allow_multi);
-    if (a.A == 9) {
-      const int cus = compute_units();
-      if (cus > 0 && a.B >= 32 * static_cast<int64_t>(cus))
-        return launch_shape<9, 32, float>(a, mode, st, num_workgroups, allow_multi);
-      return launch_shape<9, 16, float>(a, mode, st, num_workgroups, allow_multi);
-    }
+                        int64_t* num_workgroups, const TileRule& rule) {
+  const int cus = compute_units();
+  if (cus <= 0) return hipErrorInvalidDevice;
+  int lanes = 16;
+  if (rule.time_parallel) {
+    lanes = kTileThreads / one_chunk_steps(a.T);
   } else {
-    if (a.A == 18) {
-      const int cus = compute_units();
-      if (a.B <= 32 || (cus > 0 && a.B >= 64 * static_cast<int64_t>(cus)))
-        return launch_shape<18, 32, uint16_t>(a, mode, st, num_workgroups, allow_multi);
-      return launch_shape<18, 16, uint16_t>(a, mode, st, num_workgroups, allow_multi);
+    // Batches of A = 9 or 18 that fill the chip in whole generations take the
+    // long-run shapes of tiled_long_f32.hip and tiled_long_bf16.hip (32 to 128
+    // lanes, chunks of 8 or 4 steps).
+    if (rule.shapes && (a.A == 9 || a.A == 18)) {
+      hipError_t err = hipSuccess;
+      const bool launched = lt == LogitsType::F32
+                                ? launch_tiled_long_f32(a, mode, st, num_workgroups, rule.multi, &err)
+                                : launch_tiled_long_bf16(a, mode, st, num_workgroups, rule.multi, &err);
+      if (launched) return err;
     }
-    if (a.A == 9) return launch_shape<9, 16, uint16_t>(a, mode, st, num_workgroups, allow_multi);
+    if (rule.shapes) lanes = tile_lanes(a, cus, rule.one_chunk);
+    if (lanes == 16 && wide_tiles(a, lt, cus, a.T <= 16 || !rule.shapes)) {
+      if (a.A == 9) return launch_shape<9, 32, float>(a, mode, st, num_workgroups, rule.multi);
+      return launch_shape<18, 32, uint16_t>(a, mode, st, num_workgroups, rule.multi);
+    }
   }
-  // The other action counts, 16 lanes per workgroup (instantiated in three
-  // more files, which compile in parallel).
-  if (a.A >= 2 && a.A <= 8) return launch_tiled_a2_8(a, lt, mode, st, num_workgroups, allow_multi);
-  if (a.A >= 10 && a.A <= 14) return launch_tiled_a10_14(a, lt, mode, st, num_workgroups, allow_multi);
+  while (lanes > a.B || !rows_fit(a, kTileThreads / lanes)) {
+    // (tiled_supported: 16 lanes fit.)
+    lanes = lanes > a.B ? lanes / 2 : lanes * 2;
+  }
+  if (a.A == 18) return launch_any<18>(a, lt, lanes, mode, st, num_workgroups, rule.multi);
+  if (a.A == 9) return launch_any<9>(a, lt, lanes, mode, st, num_workgroups, rule.multi);
+  // The other action counts are instantiated in three more files, which
+  // compile in parallel.
+  if (a.A >= 2 && a.A <= 8) return launch_tiled_a2_8(a, lt, lanes, mode, st, num_workgroups, rule.multi);
+  if (a.A >= 10 && a.A <= 14) return launch_tiled_a10_14(a, lt, lanes, mode, st, num_workgroups, rule.multi);
   if (a.A >= 15 && a.A <= kTiledMaxActions)
-    return launch_tiled_a15_20(a, lt, mode, st, num_workgroups, allow_multi);
+    return launch_tiled_a15_20(a, lt, lanes, mode, st, num_workgroups, rule.multi);
   return hipErrorNotSupported;
 }
 
