@@ -469,7 +469,7 @@ vtrace_status vtrace_head_loss_grad(
     return VTRACE_ERR_ALIGN;
   if (!workspace) return VTRACE_ERR_WORKSPACE;
   if (!aligned(workspace, 16)) return VTRACE_ERR_ALIGN;
-  if (workspace_bytes < vtrace::head_workspace_bytes(B, A, H)) return VTRACE_ERR_WORKSPACE;
+  if (workspace_bytes < vtrace::head_workspace_least_bytes(B, A, H)) return VTRACE_ERR_WORKSPACE;
 
   vtrace::HeadArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -505,7 +505,7 @@ vtrace_status vtrace_head_loss_grad(
   a.pg_adv = pg_advantages;
   a.lane_losses = lane_losses;
   a.outputs = outputs;
-  vtrace::head_attach_workspace(&a, workspace);
+  vtrace::head_attach_workspace(&a, workspace, workspace_bytes);
   (void)hipGetLastError();
   return vtrace::launch_head(a, as_hip(stream)) == hipSuccess ? VTRACE_OK : VTRACE_ERR_HIP;
 }

@@ -31,6 +31,7 @@ struct HeadArgs {
   int behaviour_bf16;  // behaviour logits are bfloat16
   int reward_transform;
   int grad_bf16;       // d_hidden is written as bfloat16
+  int split;           // a workgroup's waves share one lane (head_attach_workspace)
   // outputs
   float* losses;       // [4]
   void* d_hidden;      // [T,B,H]
@@ -47,7 +48,7 @@ struct HeadArgs {
 };
 
 // The fused output-layer kernel runs at most this many workgroups (two per CU
-// of a 256-CU part); each loops over groups of four lanes.
+// of a 256-CU part); each loops over groups of four lanes, or (split) over lanes.
 constexpr int64_t kHeadMaxWorkgroups = 512;
 // Hidden sizes with a kernel instance, and the largest A (A + 1 output columns
 // fill at most two 16-column MFMA tiles).
@@ -57,11 +58,17 @@ constexpr int64_t kHeadMaxActions = 31;
 // 0xFFFFF000 bytes, so B*H is at most this.
 constexpr int64_t kHeadMaxBatchTimesHidden = 0xFFFFF000LL / 64;
 bool head_hidden_supported(int64_t H);
-int64_t head_workgroups(int64_t B);
+constexpr int kHeadLanes = 4;
 // Workspace of the fused kernel: the 256-byte header, then float64 loss
-// partials and float32 gradient partials per workgroup.
+// partials and float32 gradient partials per workgroup; enough for a workgroup
+// per lane, and the least a call accepts (a workgroup per four lanes).
 size_t head_workspace_bytes(int64_t B, int64_t A, int64_t H);
-void head_attach_workspace(HeadArgs* a, void* ws);
+size_t head_workspace_least_bytes(int64_t B, int64_t A, int64_t H);
+// Sets the workspace pieces and, for a workspace of this size, `split`.
+void head_attach_workspace(HeadArgs* a, void* ws, size_t bytes);
 hipError_t launch_head(const HeadArgs& a, hipStream_t s);
+void launch_head_h64(const HeadArgs& a, hipStream_t s, unsigned nwg);
+void launch_head_h128(const HeadArgs& a, hipStream_t s, unsigned nwg);
+void launch_head_h256(const HeadArgs& a, hipStream_t s, unsigned nwg);
 
 }  // namespace vtrace
