@@ -9,18 +9,19 @@ namespace {
 int head_columns(int64_t A) { return A + 1 > 16 ? 32 : 16; }
 
 // Adds the workgroups' partial sums in a fixed order (float64): d_W, d_bias and
-// the loss totals.  Block i covers 64 outputs; each of its 16 waves sums the
-// workgroups k = wave, wave + 16, ... (one coalesced 256-byte row per step),
-// and the 16 wave sums are added in wave order.
-constexpr int kFinishOutputs = 64;
+// the loss totals.  Block i covers 32 outputs; each of its 32 half-waves sums the
+// workgroups k = half-wave, half-wave + 32, ... (one 128-byte line per step), and
+// the 32 sums are added in order.
+constexpr int kFinishOutputs = 32;
 constexpr int kFinishWaves = 16;
+constexpr int kFinishParts = kFinishWaves * kWave / kFinishOutputs;
 __global__ __launch_bounds__(kFinishWaves* kWave) void head_finish_kernel(HeadArgs a, int C, int nwg) {
-  __shared__ double s_q[kFinishWaves][kFinishOutputs];
+  __shared__ double s_q[kFinishParts][kFinishOutputs];
   const int64_t H = a.H;
   const int A1 = static_cast<int>(a.A) + 1;
   const int64_t n_w = H * A1;
   const int64_t n_out = n_w + A1;
-  const int wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int part = threadIdx.x / kFinishOutputs, lane = threadIdx.x % kFinishOutputs;
   const int64_t i = static_cast<int64_t>(blockIdx.x) * kFinishOutputs + lane;
   const size_t stride = static_cast<size_t>(H + 1) * C;
   size_t off = 0;
@@ -33,13 +34,13 @@ __global__ __launch_bounds__(kFinishWaves* kWave) void head_finish_kernel(HeadAr
     // Unrolled so that several rows' loads are in flight; the additions keep
     // their order.
 #pragma unroll 8
-    for (int k = wv; k < nwg; k += kFinishWaves) sum += static_cast<double>(a.grad_partials[k * stride + off]);
+    for (int k = part; k < nwg; k += kFinishParts) sum += static_cast<double>(a.grad_partials[k * stride + off]);
   }
-  s_q[wv][lane] = sum;
+  s_q[part][lane] = sum;
   __syncthreads();
-  if (wv == 0 && i < n_out) {
+  if (part == 0 && i < n_out) {
     double tot = 0.0;
-    for (int q = 0; q < kFinishWaves; ++q) tot += s_q[q][lane];
+    for (int q = 0; q < kFinishParts; ++q) tot += s_q[q][lane];
     if (i < n_w)
       a.d_weight[i] = static_cast<float>(tot);
     else

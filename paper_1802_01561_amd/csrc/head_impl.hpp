@@ -41,13 +41,22 @@
 //     are written to LDS, and after a workgroup barrier wave w accumulates
 //     rows [w H/4, (w+1) H/4) of d_W over the four lanes' tiles with 16x16x32
 //     MFMAs (operands by transposing reads), in registers, for the whole walk (wave 0 also d_bias, with a ones
-//     operand).  A second kernel adds the workgroups' partial sums.
+//     operand).  A second kernel adds the workgroups' partial sums.  (Transposing
+//     reads and 32-deep products in place of 128 two-byte reads and 16-deep ones
+//     per chunk: T = 1000, B = 2048, A = 18, H = 256, bf16 d_hidden 628 -> 564 us.)
+//
+// Large batches are bound by HBM with float32 d_hidden (3.3 GB in 714 us there,
+// 4.6 TB/s) and by the two waves per SIMD that registers and LDS allow with
+// bfloat16 (543 us, 4.2 TB/s); the first chunk of a workgroup and the final sums
+// cost about 35 us of the 156 that T = 100, B = 4096 takes (186 when the weights
+// were loaded one by one first and every lane group waited for its first chunk).
 //
 // Small batches (kSplit): a workgroup's four waves take four consecutive chunks
 // of one lane instead of one chunk of four lanes, so that a batch of B lanes
 // gives B workgroups and a quarter of the chunks one after another.  Each wave
 // then also needs V(x) at the next wave's first step and the later waves'
-// composite of the recursion, exchanged through LDS with two more barriers.
+// composite of the recursion, exchanged through LDS with two more barriers
+// (T = 100, B = 32, A = 9, H = 256: 47 -> 19 us).
 #pragma once
 
 #include <type_traits>
@@ -165,6 +174,8 @@ __device__ __forceinline__ bf16x8 read_columns(const uint16_t* tile, int pitch, 
 // prefetched loads alone (vmcnt(n)) rather than for every store before them.
 typedef __amdgpu_buffer_rsrc_t Rsrc;
 constexpr int kRawBufferFlags = 0x00020000;  // raw buffer, 32-bit elements, no swizzle
+constexpr int kNonTemporal = 2;  // raw buffer cache policy
+constexpr int kRowRor8 = 0x128;  // DPP: thread i of a row reads thread i ^ 8
 constexpr uint32_t kOutOfRange = 0xFFFFF000u;  // beyond every descriptor used here
 
 __device__ __forceinline__ Rsrc make_rsrc(const void* base, uint32_t bytes) {
@@ -221,20 +232,6 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_kernel(HeadArgs a) {
   const int64_t T = a.T, B = a.B, A = a.A;
   const int A1 = static_cast<int>(A) + 1;
 
-  // The layer's weights, twice: W^T for the forward, W in K-slot order for
-  // d_hidden.  Columns beyond the baseline are zero.
-  for (int i = tid; i < H * C; i += kHeadThreads) {
-    const int h = i / C, c = i % C;
-    const uint16_t v = c < A1 ? a.weight[static_cast<int64_t>(h) * A1 + c] : uint16_t(0);
-    s_wt[c * S::WT_PITCH + h] = v;
-    s_wp[h * S::WP_PITCH + slot_of_column<NT>(c)] = v;
-  }
-  if (tid < C) {
-    s_bias[tid] = tid < A1 ? a.bias[tid] : 0.0f;
-    s_db[tid] = 0.0f;
-  }
-  __syncthreads();
-
   const bool beh_lp = a.behaviour_log_probs != 0;
   const bool no_ratio = a.correction == kCorrNone || a.correction == kCorrEpsilon;
   const bool use_y = !beh_lp && !no_ratio;
@@ -254,6 +251,18 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_kernel(HeadArgs a) {
   const uint32_t row_s = static_cast<uint32_t>(B * 4);
   const uint32_t row_y = static_cast<uint32_t>(B * A * sizeof(BehIn));
   const uint32_t row_o = static_cast<uint32_t>(B * A1 * 4);
+  // This thread's byte offsets in a chunk that starts at its descriptor's first
+  // row: step s's row, and for d_hidden the row and piece it stores (below).  Kept
+  // over the walk (the empty statements hide what they are made of): formed anew,
+  // they are multiply-adds whose unused upper halves lie in registers with loads
+  // in flight, for which each of them then waits.
+  const bool low = s < 8;
+  uint32_t off_h = s * row_h + 16u * g;
+  uint32_t off_y = s * row_y + 4u * g * static_cast<uint32_t>(sizeof(BehIn));
+  uint32_t off_s = s * row_s;
+  uint32_t off_o = s * row_o + 16u * g;
+  uint32_t off_d = (s % 8) * row_d + (low ? 0u : 64u) + 16u * g;
+  asm volatile("" : "+v"(off_h), "+v"(off_y), "+v"(off_s), "+v"(off_o), "+v"(off_d));
   // A descriptor over a chunk's rows of a [T, B, n] array, starting at lane
   // b of the chunk's first existing row and cut at the array's end, so that
   // no offset it accepts lies outside the array.
@@ -274,68 +283,99 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_kernel(HeadArgs a) {
   });
   double wave_pg = 0.0, wave_base = 0.0, wave_ent = 0.0;
 
-  for (int64_t group = xcd_tile(blockIdx.x, gridDim.x); group < ngroups; group += gridDim.x) {
-    const int64_t b = kSplit ? group : group * kHeadWaves + w;
+  auto lane_of = [&](int64_t group) { return kSplit ? group : group * kHeadWaves + w; };
+  // Register prefetch of one chunk: this lane's hidden slice, behaviour
+  // values and per-step scalars.
+  v4u hreg[S::KS];
+  float yreg[NT][4];
+  int32_t p_act = 0;
+  float p_r = 0.f, p_g = 0.f, p_lmu = 0.f, p_boot = 0.f;
+  // Descriptors of a chunk start at its first existing row (wave-uniform);
+  // lane s of the row group reads row t0 + s at offset rel * row stride.
+  auto prefetch = [&](KernelArgs& a, int64_t group, int k) {
+    const int64_t b = lane_of(group);
+    const bool lane_ok = b < B;
+    const int64_t t0 = first_step(k);
+    const int64_t tb = t0 < 0 ? 0 : t0;
+    const bool row_ok = t0 + s >= 0;
+    const uint32_t skip = static_cast<uint32_t>(t0 - tb);  // rows before t = 0, negative
+    const int64_t brow = tb * B + b;
+    const Rsrc rh = chunk_rsrc(a.hidden, H, 2, brow, lane_ok);
+    const uint32_t oh = row_ok ? off_h + skip * row_h : kOutOfRange;
+    static_for<S::KS>([&](auto J) {
+      constexpr int j = decltype(J)::value;
+      hreg[j] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rh, oh + 64 * j, 0, 0));
+    });
+    const uint32_t os = row_ok ? off_s + skip * row_s : kOutOfRange;
+    p_act = static_cast<int32_t>(
+        __builtin_amdgcn_raw_buffer_load_b32(chunk_rsrc(a.actions, 1, 4, brow, lane_ok), os, 0, 0));
+    p_r = buffer_load_f32(chunk_rsrc(a.rewards, 1, 4, brow, lane_ok), os);
+    p_g = buffer_load_f32(chunk_rsrc(a.discounts, 1, 4, brow, lane_ok), os);
+    p_lmu = buffer_load_f32(chunk_rsrc(a.behaviour, 1, 4, brow, lane_ok && beh_lp && !no_ratio), os);
+    p_boot = buffer_load_f32(make_rsrc(a.bootstrap_value + (lane_ok ? b : 0), 4u), k == 0 && lane_ok ? 0u : kOutOfRange);
+    // Behaviour logits: one offset per lane, the columns in the instruction
+    // offset.  Columns >= A (the tiles' padding) get an offset beyond the
+    // descriptor, so they read nothing (they would be the next lane's row).
+    const Rsrc ry = chunk_rsrc(a.behaviour, A, sizeof(BehIn), brow, lane_ok && use_y);
+    const uint32_t oy = row_ok ? off_y + skip * row_y : kOutOfRange;
+    static_for<NT>([&](auto CT) {
+      constexpr int ct = decltype(CT)::value;
+      static_for<4>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        const bool col_ok = 16 * ct + 4 * g + i < A;
+        yreg[ct][i] = buffer_load_logit<BehIn>(ry, col_ok ? oy + (16 * ct + i) * sizeof(BehIn) : kOutOfRange);
+      });
+    });
+  };
+
+  const int64_t first_group = xcd_tile(blockIdx.x, gridDim.x);
+  prefetch(*fresh_args(), first_group, 0);
+  // The layer's weights, twice: W^T for the forward, W in K-slot order for
+  // d_hidden.  Columns beyond the baseline are zero.  (All of a thread's loads go
+  // out before its first LDS write, and the first chunk's before them.)
+  {
+    constexpr int kPerThread = H * C / kHeadThreads;
+    uint16_t v[kPerThread];
+    static_for<kPerThread>([&](auto I) {
+      const int i = tid + decltype(I)::value * kHeadThreads;
+      const int h = i / C, c = i % C;
+      v[decltype(I)::value] = a.weight[h * A1 + (c < A1 ? c : A1 - 1)];
+    });
+    static_for<kPerThread>([&](auto I) {
+      const int i = tid + decltype(I)::value * kHeadThreads;
+      const int h = i / C, c = i % C;
+      const uint16_t x = c < A1 ? v[decltype(I)::value] : uint16_t(0);
+      s_wt[c * S::WT_PITCH + h] = x;
+      s_wp[h * S::WP_PITCH + slot_of_column<NT>(c)] = x;
+    });
+  }
+  if (tid < C) {
+    s_bias[tid] = tid < A1 ? a.bias[tid] : 0.0f;
+    s_db[tid] = 0.0f;
+  }
+  __syncthreads();
+
+  for (int64_t group = first_group; group < ngroups; group += gridDim.x) {
+    const int64_t b = lane_of(group);
     const bool lane_ok = kSplit || b < B;
-    const double boot = lane_ok ? static_cast<double>(a.bootstrap_value[b]) : 0.0;
+    // Wait for the group's first chunk here (it was loaded during the previous
+    // group's last): the chunk loop's first use of the prefetched registers is
+    // then reached from the loop entry with nothing outstanding, and the
+    // compiler's wait there only has to cover the previous iteration's loads, not
+    // the stores issued after them.
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    const double boot = static_cast<double>(p_boot);
     double cy_V = boot, cy_v = boot, cy_A = 0.0;
     double l_pg = 0.0, l_base = 0.0, l_ent = 0.0;
     bool bad_action = false;
 
-    // Register prefetch of one chunk: this lane's hidden slice, behaviour
-    // values and per-step scalars.
-    v4u hreg[S::KS];
-    float yreg[NT][4];
-    int32_t p_act = 0;
-    float p_r = 0.f, p_g = 0.f, p_lmu = 0.f;
-    // Descriptors of a chunk start at its first existing row (wave-uniform);
-    // lane s of the row group reads row t0 + s at offset rel * row stride.
-    auto prefetch = [&](KernelArgs& a, int k) {
-      const int64_t t0 = first_step(k);
-      const int64_t tb = t0 < 0 ? 0 : t0;
-      const bool row_ok = t0 + s >= 0;
-      const uint32_t rel = static_cast<uint32_t>(t0 + s - tb);
-      const int64_t brow = tb * B + b;
-      const Rsrc rh = chunk_rsrc(a.hidden, H, 2, brow, lane_ok);
-      const uint32_t oh = row_ok ? rel * row_h + 16u * g : kOutOfRange;
-      static_for<S::KS>([&](auto J) {
-        constexpr int j = decltype(J)::value;
-        hreg[j] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rh, oh + 64 * j, 0, 0));
-      });
-      const uint32_t os = row_ok ? rel * row_s : kOutOfRange;
-      p_act = static_cast<int32_t>(
-          __builtin_amdgcn_raw_buffer_load_b32(chunk_rsrc(a.actions, 1, 4, brow, lane_ok), os, 0, 0));
-      p_r = buffer_load_f32(chunk_rsrc(a.rewards, 1, 4, brow, lane_ok), os);
-      p_g = buffer_load_f32(chunk_rsrc(a.discounts, 1, 4, brow, lane_ok), os);
-      p_lmu = buffer_load_f32(chunk_rsrc(a.behaviour, 1, 4, brow, lane_ok && beh_lp && !no_ratio), os);
-      // Behaviour logits: one offset per lane, the columns in the instruction
-      // offset.  Columns >= A (the tiles' padding) get an offset beyond the
-      // descriptor, so they read nothing (they would be the next lane's row).
-      const Rsrc ry = chunk_rsrc(a.behaviour, A, sizeof(BehIn), brow, lane_ok && use_y);
-      const uint32_t oy = row_ok ? rel * row_y + 4u * g * static_cast<uint32_t>(sizeof(BehIn)) : kOutOfRange;
-      static_for<NT>([&](auto CT) {
-        constexpr int ct = decltype(CT)::value;
-        static_for<4>([&](auto I) {
-          constexpr int i = decltype(I)::value;
-          const bool col_ok = 16 * ct + 4 * g + i < A;
-          yreg[ct][i] = buffer_load_logit<BehIn>(ry, col_ok ? oy + (16 * ct + i) * sizeof(BehIn) : kOutOfRange);
-        });
-      });
-    };
-
-    prefetch(*fresh_args(), 0);
-    // Wait for the first chunk here, once per lane: the loop's first use of
-    // the prefetched registers is then reached from the loop entry with
-    // nothing outstanding, and the compiler's wait there only has to cover
-    // the previous iteration's loads, not the stores issued after them.
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     for (int k = 0; k < nchunks; ++k) {
       KernelArgs& a = *fresh_args();
       const int64_t t0 = first_step(k);
       const int64_t t = t0 + s;
       const bool step_ok = lane_ok && t >= 0;
       const int64_t tb = t0 < 0 ? 0 : t0;
-      const uint32_t rel = static_cast<uint32_t>(t - tb);
+      const uint32_t skip = static_cast<uint32_t>(t0 - tb);  // rows before t = 0, negative
       const int64_t brow = tb * B + b;
 
       // 1. Forward product, from the prefetched hidden slice.
@@ -404,9 +444,10 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_kernel(HeadArgs a) {
       // other wave's matrix products on the same SIMD: 6.64-6.65 -> 6.25-6.26
       // ms at the stress shape with float32 d_hidden; with bf16 d_hidden it
       // measured 0.6% slower and keeps normal priority.
-      if (k + 1 < nchunks) {
+      const bool last_chunk = k + 1 == nchunks;
+      if (!last_chunk || group + gridDim.x < ngroups) {
         if constexpr (!kBf16Grad) __builtin_amdgcn_s_setprio(2);
-        prefetch(a, k + 1);
+        prefetch(a, last_chunk ? group + gridDim.x : group, last_chunk ? 0 : k + 1);
         if constexpr (!kBf16Grad) __builtin_amdgcn_s_setprio(0);
       }
 
@@ -434,7 +475,7 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_kernel(HeadArgs a) {
           static_for<4>([&](auto I) {
             constexpr int i = decltype(I)::value;
             const int c = 16 * ct + 4 * g + i;
-            buffer_store_f32(o[ct][i], ro, (step_ok && c < A1) ? rel * row_o + 4u * c : kOutOfRange);
+            buffer_store_f32(o[ct][i], ro, (step_ok && c < A1) ? off_o + skip * row_o + 4u * (16 * ct + i) : kOutOfRange);
           });
         });
       }
@@ -571,7 +612,7 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_kernel(HeadArgs a) {
       }
 
       {
-        const uint32_t o1 = (step_ok && g == 0) ? rel * row_s : kOutOfRange;
+        const uint32_t o1 = (step_ok && g == 0) ? off_s + skip * row_s : kOutOfRange;
         buffer_store_f32(static_cast<float>(v_t), chunk_rsrc(a.vs, 1, 4, brow, lane_ok && a.vs), o1);
         buffer_store_f32(static_cast<float>(adv), chunk_rsrc(a.pg_adv, 1, 4, brow, lane_ok && a.pg_adv), o1);
       }
@@ -620,22 +661,49 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_kernel(HeadArgs a) {
       // into one 16-byte store).  Either way the four lane groups write 64
       // contiguous bytes of each row per instruction.
       const int grow = (kL * w + s) * S::GL_PITCH;
-      const uint32_t od = step_ok ? rel * row_d : kOutOfRange;
       const Rsrc rd = chunk_rsrc(a.d_hidden, H, gsz, brow, lane_ok);
       // M row (hidden unit) that operand lane s supplies in M tile i.
       auto m_row = [&](int i) {
         return kBf16Grad ? 32 * (i / 2) + 8 * (s / 4) + 4 * (i % 2) + (s % 4) : 16 * i + s;
       };
-      f32x4 prev = {0.f, 0.f, 0.f, 0.f};
-      auto store_dh = [&](f32x4 acc, int i) {
-        if constexpr (!kBf16Grad) {
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, acc), rd,
-                                                 od + 4u * (16u * i + 4u * g), 0, 0);
+      // Two neighbouring 64-byte pieces of every step's row make a 128-byte line,
+      // and the 16 threads of a group trade halves of them between steps s and
+      // s ^ 8 so that one store writes eight steps' whole lines and the next the
+      // other eight's.
+      // (T = 1000, B = 2048, A = 18, H = 256: float32 776 -> 727 us, bfloat16 572
+      // -> 555.)  Whole lines also let bfloat16 stores carry the non-temporal
+      // hint (555 -> 548 us); for float32 it cost 4% there (727 -> 758).
+      constexpr int kStoreAux = kBf16Grad ? kNonTemporal : 0;
+      const int64_t t_lo = t0 + s % 8;
+      const uint32_t od_lo = lane_ok && t_lo >= 0 ? off_d + skip * row_d : kOutOfRange;
+      const uint32_t od_hi = lane_ok && t_lo + 8 >= 0 ? off_d + (skip + 8) * row_d : kOutOfRange;
+      v4u piece = {0u, 0u, 0u, 0u};
+      auto store_piece = [&](v4u x, auto N) {
+        constexpr int n = decltype(N)::value;  // 64-byte piece of the row
+        if constexpr (n % 2 == 0) {
+          piece = x;
         } else {
-          if (i % 2 == 1) {
+          v4u first, second;
+          for (int e = 0; e < 4; ++e) {
+            const unsigned other = static_cast<unsigned>(__builtin_amdgcn_update_dpp(
+                0, static_cast<int>(low ? x[e] : piece[e]), kRowRor8, 0xF, 0xF, true));
+            first[e] = low ? piece[e] : other;
+            second[e] = low ? other : x[e];
+          }
+          __builtin_amdgcn_raw_buffer_store_b128(first, rd, od_lo + 64u * (n - 1), 0, kStoreAux);
+          __builtin_amdgcn_raw_buffer_store_b128(second, rd, od_hi + 64u * (n - 1), 0, kStoreAux);
+        }
+      };
+      f32x4 prev = {0.f, 0.f, 0.f, 0.f};
+      auto store_dh = [&](f32x4 acc, auto I) {
+        constexpr int i = decltype(I)::value;
+        if constexpr (!kBf16Grad) {
+          store_piece(__builtin_bit_cast(v4u, acc), I);
+        } else {
+          if constexpr (i % 2 == 1) {
             const v4u pk = {pack_bf16x2(prev[0], prev[1]), pack_bf16x2(prev[2], prev[3]),
                             pack_bf16x2(acc[0], acc[1]), pack_bf16x2(acc[2], acc[3])};
-            __builtin_amdgcn_raw_buffer_store_b128(pk, rd, od + 2u * (32u * (i / 2) + 8u * g), 0, 0);
+            store_piece(pk, std::integral_constant<int, i / 2>{});
           }
           prev = acc;
         }
@@ -655,7 +723,7 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_kernel(HeadArgs a) {
           const bf16x8 wv = *reinterpret_cast<const bf16x8*>(&s_wp[m_row(i) * S::WP_PITCH + 8 * g]);
           f32x4 acc = mfma_k32(wv, ghi, f32x4{0.f, 0.f, 0.f, 0.f});
           acc = mfma_k32(wv, glo, acc);
-          store_dh(acc, i);
+          store_dh(acc, I);
         });
       } else {
         const f32x4 gf = {Gv[0][0], Gv[0][1], Gv[0][2], Gv[0][3]};
@@ -669,7 +737,7 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_kernel(HeadArgs a) {
           const s16x4 wv = *reinterpret_cast<const s16x4*>(&s_wp[m_row(i) * S::WP_PITCH + 4 * g]);
           f32x4 acc = mfma_k16(wv, shi, f32x4{0.f, 0.f, 0.f, 0.f});
           acc = mfma_k16(wv, slo, acc);
-          store_dh(acc, i);
+          store_dh(acc, I);
         });
       }
 
