@@ -37,7 +37,8 @@ HEAD_COUNTERS_FILE = os.path.join(ROOT, "profiles", "head_stress_counters.json")
 # The sources each counted kernel is built from.
 PLAIN_SOURCES = ("tiled.hip", "tiled_long_f32.hip", "tiled_impl.hpp", "row_stats.hpp", "device_common.hpp",
                  "wave_ops.hpp", "launch.hpp")
-HEAD_SOURCES = ("head.hip", "head.hpp", "device_common.hpp", "wave_ops.hpp", "launch.hpp")
+HEAD_SOURCES = ("head.hip", "head_impl.hpp", "head_h256.hip", "head.hpp", "device_common.hpp", "wave_ops.hpp",
+                "launch.hpp")
 
 
 def parse_args():
