@@ -73,27 +73,50 @@ __device__ __forceinline__ float read_row_max(const In* r, float (&v)[A_]) {
   return m;
 }
 
-// Whether every row of the wave is finite (its maximum m and its minimum
-// both finite): then no exponent-sum term needs the clamp against -inf and
-// NaN logits, and the whole wave takes the unclamped terms (A + 1 VALU
-// instructions fewer per row for the A - 1 that find its minimum, fewer for
-// three-operand minima).  Called by every thread of the wave.
+// The unclamped exponent-sum terms (exp2_f64_term) are right for a row whose
+// logits all lie within kMostBelow of a maximum smaller than kMostMaximum: their
+// exponents fit the integer word that scales a term, and neither the rounding of
+// m_z log2 e nor, in the gradient, that of the float32 entropy_cost m_z shows.
+// Masks of illegal actions (-1e9 and down to the type's lowest value, or -inf) and
+// rows of masks alone lie beyond.  row_plain tells, from the row's maximum m and
+// its minimum (A - 1 VALU instructions, fewer with three operands; a NaN compares
+// false), so that ordinary rows need no clamp on each term.
+constexpr float kMostBelow = 7e8f, kMostMaximum = 2048.0f;
 template <int A_>
-__device__ __forceinline__ bool wave_rows_finite(const float (&v)[A_], float m) {
+__device__ __forceinline__ bool row_plain(const float (&v)[A_], float m) {
   float mn = v[0];
 #pragma unroll
   for (int j = 1; j < A_; ++j) mn = __builtin_elementwise_minimum(mn, v[j]);
-  return __all(__builtin_isfinite(mn) && __builtin_isfinite(m)) != 0;
+  return mn - m > -kMostBelow && __builtin_fabsf(m) < kMostMaximum;
+}
+
+// Brings any row with a finite maximum within those bounds without changing its
+// softmax, and returns the new maximum: logits more than 1e4 below it are raised
+// to there, where their exponentials are 0 all the same, and a row with a large
+// maximum is shifted by it (a float32 difference: exact for logits within a factor
+// of two of it, and the others' exponentials are 0).  -inf logits become zero-probability actions;
+// *any_inf tells.
+template <int A_>
+__device__ __forceinline__ float bring_within(float (&v)[A_], float m, bool* any_inf) {
+  const float shift = __builtin_fabsf(m) < kMostMaximum ? 0.0f : m;
+  const float least = (m - shift) - 1e4f;
+  bool inf = false;
+#pragma unroll
+  for (int j = 0; j < A_; ++j) {
+    inf = inf || v[j] == -INFINITY;
+    v[j] = fmaxf(v[j] - shift, least);
+  }
+  *any_inf = inf;
+  return m - shift;
 }
 
 // The rest of a target row's precise statistics (all of RowStats but the
-// ratio) from its maximum mz, its logit at the taken action za, the sums
-// sz = sum_j e_j and ed = sum_j e_j (z_j - m_z) log2 e, and ea = e_a.
-__device__ __forceinline__ void finish_target_stats(RowStats& st, float mz, float za, double sz, double ed,
+// ratio) from its maximum mz, dza = z_a - m_z, the sums sz = sum_j e_j and
+// ed = sum_j e_j (z_j - m_z) log2 e, and ea = e_a.
+__device__ __forceinline__ void finish_target_stats(RowStats& st, float mz, double dza, double sz, double ed,
                                                     double ea) {
   st.mz = mz;
   if (!__builtin_isfinite(mz)) sz = NAN;
-  const double dza = static_cast<double>(za) - static_cast<double>(mz);  // exact
   // 1/s from the hardware reciprocal and two Newton steps.
   double inv = __builtin_amdgcn_rcp(sz);
   inv = fma(inv, fma(-sz, inv, 1.0), inv);
@@ -111,40 +134,58 @@ __device__ __forceinline__ void finish_target_stats(RowStats& st, float mz, floa
   st.dza = dza;
 }
 
+// A row beyond the plain terms' bounds is brought within them and written back, so
+// that later readers see the logits that go with st.mz.  Its -inf logits, as
+// inputs whose logarithm the entropy takes, make the entropy and with it the
+// gradient row NaN.  (The terms stand in both branches: behind one that changes
+// the row, a single copy took T = 1000, B = 512, A = 18 40 -> 42 us.)
 template <int A_, typename In>
-__device__ __forceinline__ RowStats target_row_stats(const In* zr, int act_c, float* e, float* zo) {
+__device__ __forceinline__ RowStats target_row_stats(In* zr, int act_c, float* e, float* zo) {
   RowStats st;
   const float za = logit_to_float(zr[act_c]);
   float z[A_];
-  const float mz = read_row_max<A_>(zr, z);
+  const float m = read_row_max<A_>(zr, z);
   if (zo != nullptr) {
 #pragma unroll
     for (int j = 0; j < A_; ++j) zo[j] = z[j];
   }
-  const double mzl = static_cast<double>(mz) * kLog2eF64;
   // The sums start from -0.0, the additive identity, which lets the compiler
   // drop the first addition.
   double sz = -0.0;
   double ed = -0.0;  // sum_j e_j (z_j - m_z) log2 e, for the entropy
   double ea;
-  auto terms = [&](auto clamp) {
-    constexpr bool kClamp = decltype(clamp)::value;
+  auto terms = [&](const float (&x)[A_], float mx, float xa) {
+    const double mxl = static_cast<double>(mx) * kLog2eF64;
     static_for<A_>([&](auto J) {
       constexpr int j = decltype(J)::value;
-      const double xj = fma(static_cast<double>(z[j]), kLog2eF64, -mzl);
-      const double ej = exp2_f64_term<kClamp>(xj);
+      const double xj = fma(static_cast<double>(x[j]), kLog2eF64, -mxl);
+      const double ej = exp2_f64_term<false>(xj);
       sz += ej;
       e[j] = static_cast<float>(ej);
       ed = fma(ej, xj, ed);
       asm volatile("" : "+v"(sz), "+v"(ed));
     });
-    ea = exp2_f64_term<kClamp>(fma(static_cast<double>(za), kLog2eF64, -mzl));
+    ea = exp2_f64_term<false>(fma(static_cast<double>(xa), kLog2eF64, -mxl));
   };
-  if (wave_rows_finite<A_>(z, mz))
-    terms(std::false_type{});
-  else
-    terms(std::true_type{});
-  finish_target_stats(st, mz, za, sz, ed, ea);
+  float mz = m;
+  bool any_inf = false;
+  if (row_plain<A_>(z, m)) {
+    terms(z, m, za);
+  } else {
+    mz = bring_within<A_>(z, m, &any_inf);
+#pragma unroll
+    for (int j = 0; j < A_; ++j) {
+      if (zo != nullptr) zo[j] = z[j];
+      if constexpr (std::is_same_v<In, float>)
+        zr[j] = z[j];
+      else
+        zr[j] = to_bf16(z[j]);
+    }
+    terms(z, mz, logit_to_float(zr[act_c]));
+  }
+  const double dza = static_cast<double>(za) - static_cast<double>(m);  // exact
+  finish_target_stats(st, mz, dza, sz, ed, ea);
+  if (any_inf) st.H = NAN;
   return st;
 }
 
@@ -154,20 +195,22 @@ template <int A_, typename In>
 __device__ __forceinline__ double behaviour_exp_sum(const In* yr, int act_c, double* dya) {
   float y[A_];
   const float my = read_row_max<A_>(yr, y);
-  const double myl = static_cast<double>(my) * kLog2eF64;
   double sy = -0.0;
-  auto terms = [&](auto clamp) {
-    constexpr bool kClamp = decltype(clamp)::value;
+  auto terms = [&](const float (&x)[A_], float mx) {
+    const double mxl = static_cast<double>(mx) * kLog2eF64;
     static_for<A_>([&](auto J) {
       constexpr int j = decltype(J)::value;
-      sy += exp2_f64_term<kClamp>(fma(static_cast<double>(y[j]), kLog2eF64, -myl));
+      sy += exp2_f64_term<false>(fma(static_cast<double>(x[j]), kLog2eF64, -mxl));
       asm volatile("" : "+v"(sy));
     });
   };
-  if (wave_rows_finite<A_>(y, my))
-    terms(std::false_type{});
-  else
-    terms(std::true_type{});
+  if (row_plain<A_>(y, my)) {
+    terms(y, my);
+  } else {
+    bool any_inf;
+    const float m = bring_within<A_>(y, my, &any_inf);
+    terms(y, m);
+  }
   if (!__builtin_isfinite(my)) sy = NAN;
   *dya = static_cast<double>(logit_to_float(yr[act_c])) - static_cast<double>(my);
   return sy;
@@ -177,7 +220,7 @@ __device__ __forceinline__ double behaviour_exp_sum(const In* yr, int act_c, dou
 // zo (precise mode; may be null) receives the target row as float32, for
 // callers that keep it in registers until the gradient.
 template <int A_, bool kPrecise, typename In>
-__device__ __forceinline__ RowStats row_stats(const In* zr, const In* yr, int act_c, bool act_ok,
+__device__ __forceinline__ RowStats row_stats(In* zr, const In* yr, int act_c, bool act_ok,
                                               bool beh_lp, bool no_ratio, float lmu, float* e,
                                               float* zo = nullptr) {
   if constexpr (kPrecise) {

@@ -257,7 +257,8 @@ __global__ __launch_bounds__(kRowsThreads, K == 2 ? 3 : 2) void rows_kernel(Step
       const float mz = q.mz[s], za = q.za[s];
       RowStats st;
       const double ea = exp2_f64_term(fma(static_cast<double>(za), kLog2eF64, -static_cast<double>(mz) * kLog2eF64));
-      finish_target_stats(st, mz, za, q.sz[s], q.ed[s], ea);
+      const double dza = static_cast<double>(za) - static_cast<double>(mz);  // exact
+      finish_target_stats(st, mz, dza, q.sz[s], q.ed[s], ea);
       if (no_ratio) {
         st.ratio = 1.0;
       } else if (beh_lp) {

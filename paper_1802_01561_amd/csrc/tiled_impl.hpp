@@ -449,7 +449,7 @@ __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t 
     if (!step_ok) act = 0;  // rows that do not exist carry a harmless action
 
     // This thread's rows.
-    const In* zr = reinterpret_cast<const In*>(lds_z) + s * S::IN_PITCH + lane_local * A_;
+    In* zr = reinterpret_cast<In*>(lds_z) + s * S::IN_PITCH + lane_local * A_;
     const In* yr = reinterpret_cast<const In*>(lds_y) + s * S::IN_PITCH + lane_local * A_;
     const bool act_ok = act >= 0 && act < A_;
     const int act_c = act_ok ? act : 0;
