@@ -51,26 +51,25 @@ __global__ __launch_bounds__(kLaneSerialThreads) void lane_serial_kernel(StepArg
           if (j == act) ya = y;
         }
       }
-      // Exponent sums in float64 (e_j = 2^((l_j - m) log2 e), as the tiled
-      // kernel's precise mode); also sum_j e_j (z_j - m_z) in float32, which
+      // Exponent sums in float64 (e_j = 2^((l_j - m) log2 e) from the exact
+      // difference, whatever the maximum's size); also sum_j e_j (z_j - m_z) in float32, which
       // gives the entropy as H = log s - (sum_j e_j (z_j - m_z)) / s.
       constexpr double kLog2e = 1.4426950408889634;
-      const double mzl = static_cast<double>(mz) * kLog2e;
-      const double myl = static_cast<double>(my) * kLog2e;
       double sz = 0.0, sy = 0.0;
       float ed = 0.f;
       for (int64_t j = 0; j < A; ++j) {
         const float z = logit_to_float(zr[j]);
-        sz += exp2_f64_term(fma(static_cast<double>(z), kLog2e, -mzl));
+        sz += exp2_f64_term((static_cast<double>(z) - static_cast<double>(mz)) * kLog2e);
         const float dz = z - mz;
         ed += expf(dz) * dz;
-        if (!beh_lp) sy += exp2_f64_term(fma(static_cast<double>(logit_to_float(yr[j])), kLog2e, -myl));
+        if (!beh_lp)
+          sy += exp2_f64_term((static_cast<double>(logit_to_float(yr[j])) - static_cast<double>(my)) * kLog2e);
       }
       // A row whose maximum is not finite (NaN or +inf logits) gets NaN sums.
       if (!__builtin_isfinite(mz)) sz = NAN;
       if (!beh_lp && !__builtin_isfinite(my)) sy = NAN;
       const double dza = static_cast<double>(za) - static_cast<double>(mz);  // exact
-      const double ea = exp2_f64_term(fma(static_cast<double>(za), kLog2e, -mzl));
+      const double ea = exp2_f64_term(dza * kLog2e);
       const double log_pa_d = dza - log(sz);
 
       // With behaviour log-probabilities the ratio is exp(log pi(a) - log mu(a)).

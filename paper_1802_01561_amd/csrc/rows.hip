@@ -88,6 +88,12 @@ struct RowSums {
   float mz[L], my[L], za[L], ya[L];
 };
 
+// log2 e rounded to 29 bits (4.4e-10 below it, a sixth of the exponential
+// polynomial's error): the float64 products of it and a float32 logit are exact, so
+// that the fused multiply-add below forms a term's exponent from the exact
+// difference z_j - m_z, whatever the size of m_z.
+constexpr double kLog2eShort = 0x1.7154765p+0;
+
 // kEps: the epsilon-correction, whose float64 logarithm and exponential of
 // every step would cost the other calls' kernel registers.
 template <int G, int K, typename In, bool kGrad, bool kEps>
@@ -180,7 +186,7 @@ __global__ __launch_bounds__(kRowsThreads, K == 2 ? 3 : 2) void rows_kernel(Step
       const float g32 = p_g, V32 = p_V, lmu = p_lmu;
 
       // 1. This group's rows.
-      float z[R][K], e[R][K];
+      float z[R][K], e[R][K], mzr[R];
       int col_a[R];  // the row's taken action, as a column of this thread (or none)
       static_for<R>([&](auto RI) __attribute__((always_inline)) {
         constexpr int r = decltype(RI)::value;
@@ -197,11 +203,12 @@ __global__ __launch_bounds__(kRowsThreads, K == 2 ? 3 : 2) void rows_kernel(Step
         auto maximum = [](float x, float w) { return __builtin_elementwise_maximum(x, w); };
         auto add = [](double x, double w) { return x + w; };
         mz = group_reduce<G>(mz, maximum);
-        const double mzl = static_cast<double>(mz) * kLog2eF64;
+        mzr[r] = mz;
+        const double mzl = static_cast<double>(mz) * kLog2eShort;
         double sz = 0.0, ed = 0.0;
         static_for<K>([&](auto J) {
           constexpr int j = decltype(J)::value;
-          const double x = fma(static_cast<double>(z[r][j]), kLog2eF64, -mzl);
+          const double x = fma(static_cast<double>(z[r][j]), kLog2eShort, -mzl);
           const double ej = exp2_f64_term(x);
           e[r][j] = static_cast<float>(ej);
           const bool mine = c0 + j >= own;
@@ -226,12 +233,12 @@ __global__ __launch_bounds__(kRowsThreads, K == 2 ? 3 : 2) void rows_kernel(Step
           float my = y[0];
           static_for<K>([&](auto J) { my = __builtin_elementwise_maximum(my, y[decltype(J)::value]); });
           my = group_reduce<G>(my, maximum);
-          const double myl = static_cast<double>(my) * kLog2eF64;
+          const double myl = static_cast<double>(my) * kLog2eShort;
           double sy = 0.0;
           unsigned ya = 0;
           static_for<K>([&](auto J) {
             constexpr int j = decltype(J)::value;
-            const double ej = exp2_f64_term(fma(static_cast<double>(y[j]), kLog2eF64, -myl));
+            const double ej = exp2_f64_term(fma(static_cast<double>(y[j]), kLog2eShort, -myl));
             sy += c0 + j >= own ? ej : 0.0;
             ya |= col_a[r] == j ? __float_as_uint(y[j]) : 0u;
             asm volatile("" : "+v"(sy));
@@ -256,8 +263,8 @@ __global__ __launch_bounds__(kRowsThreads, K == 2 ? 3 : 2) void rows_kernel(Step
       // 2. Thread s of every wave: step t0 + s.
       const float mz = q.mz[s], za = q.za[s];
       RowStats st;
-      const double ea = exp2_f64_term(fma(static_cast<double>(za), kLog2eF64, -static_cast<double>(mz) * kLog2eF64));
       const double dza = static_cast<double>(za) - static_cast<double>(mz);  // exact
+      const double ea = exp2_f64_term(dza * kLog2eShort);
       finish_target_stats(st, mz, dza, q.sz[s], q.ed[s], ea);
       if (no_ratio) {
         st.ratio = 1.0;
@@ -328,19 +335,22 @@ __global__ __launch_bounds__(kRowsThreads, K == 2 ? 3 : 2) void rows_kernel(Step
         }
       }
 
-      // 3. d_logits_j = e_j (alpha + beta z_j) off the taken action, as in the
-      // tiled kernel; the coefficients come from the row's thread of the scan.
+      // 3. d_logits_j = e_j (alpha + beta (z_j - m_z)) off the taken action; the
+      // coefficients come from the row's thread of the scan.  (z_j - m_z and not
+      // z_j: a large common offset of a row's logits would show in the float32
+      // beta z_j.  Masked logits are held to a size that no entropy cost below 1e8
+      // takes out of float32's range; their e_j are 0.)
       // There is one such thread per row, so it forms them in float64 and rounds
       // each once: error of d_logits against float64 at A = 48 2.7e-8, 4.8e-8 with
       // float32 coefficients, in the same time (21 us at T = 100, B = 512).
       if constexpr (kGrad) {
-        const float Kz = st.mz + st.log_s - st.H;
+        const float ls_H = st.log_s - st.H;
         const double pa = ea * st.inv, ce64 = ce;
         double adv_w = adv;
         if constexpr (kEps) adv_w = adv * (pa / (pa + static_cast<double>(a.epsilon)));
         const float beta = static_cast<float>(st.inv * ce64);
-        const float alpha = static_cast<float>(st.inv * (adv_w - ce64 * Kz));
-        const double taken = ce64 * pa * (static_cast<double>(za) - Kz) - adv_w * ((st.sum - ea) * st.inv);
+        const float alpha = static_cast<float>(st.inv * (adv_w - ce64 * ls_H));
+        const double taken = ce64 * pa * (dza - ls_H) - adv_w * ((st.sum - ea) * st.inv);
         const float out_a = act_ok ? static_cast<float>(taken) : NAN;
         static_for<R>([&](auto RI) __attribute__((always_inline)) {
           constexpr int r2 = decltype(RI)::value;
@@ -350,7 +360,7 @@ __global__ __launch_bounds__(kRowsThreads, K == 2 ? 3 : 2) void rows_kernel(Step
             float x[K];
             static_for<K>([&](auto J) {
               constexpr int j = decltype(J)::value;
-              x[j] = e[r2][j] * fmaf(be, z[r2][j], al);
+              x[j] = e[r2][j] * fmaf(be, fmaxf(z[r2][j] - mzr[r2], -1e30f), al);
               if (col_a[r2] == j) x[j] = oa;
             });
             if (a.grad_bf16) {

@@ -50,10 +50,11 @@ def changed(tr):
     return tr
 
 
-# On a 256-CU part 16, 8, 2 and 1 lanes per tile.
+# On a 256-CU part 16, 8, 2 and 1 lanes per tile, the row-split and the generic kernel.
 @pytest.mark.parametrize("T,B,A,bf16", [(20, 8200, 2, False), (20, 8200, 9, True), (33, 3601, 6, False),
                                         (100, 37, 9, False), (100, 37, 20, True), (257, 37, 18, False),
-                                        (257, 37, 20, False)])
+                                        (257, 37, 20, False), (70, 37, 21, False), (70, 37, 48, True),
+                                        (20, 37, 100, False), (10, 7, 300, False)])
 @pytest.mark.parametrize("mask", MASKS)
 def test_masked_actions(T, B, A, bf16, mask):
     tr = masked_batch(T, B, A, 9500 + A + T, mask, bf16)
@@ -70,7 +71,8 @@ def test_masked_actions(T, B, A, bf16, mask):
         assert_close("targets.pg_advantages", np_out(pg), o.pg_advantages)
 
 
-@pytest.mark.parametrize("A,bf16", [(2, True), (9, False), (18, False), (20, True)])
+@pytest.mark.parametrize("A,bf16", [(2, True), (9, False), (18, False), (20, True), (21, False), (48, True), (100, False),
+                                    (300, False)])
 @pytest.mark.parametrize("variant", [{}, dict(correction="one_step_is", reward_transform="clip")])
 def test_rows_of_masks_are_uniform(A, bf16, variant):
     """Every logit of a row at one value, of any size, gives what zeros give."""
@@ -91,7 +93,7 @@ def test_rows_of_masks_are_uniform(A, bf16, variant):
             assert_close(f"rows of {value}", got, expect)
 
 
-@pytest.mark.parametrize("A", [9, 18])
+@pytest.mark.parametrize("A", [9, 18, 21, 48, 100, 300])
 def test_shifted_rows(A):
     """Rows shifted by a large common offset (a multiple of the logits' spacing there)."""
     T, B = 40, 70
@@ -109,7 +111,7 @@ def test_infinite_masks_pass_through():
     """-inf logits of actions not taken: targets as for probability 0, and NaN in
     that row's gradient and in the entropy, for every action count."""
     T, B = 40, 70
-    for A in (9, 20):
+    for A in (9, 20, 21, 100, 300):
         tr = masked_batch(T, B, A, 9800 + A, -2.0 ** 30, False)
         p = Params(2.0, 1.0, 0.9)
         ref = run_loss_grad(to_device(tr), p)
