@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import contextlib
 import ctypes
+import warnings
 from typing import NamedTuple, Optional
 
 import torch
@@ -110,11 +111,8 @@ def _variant(correction="vtrace", q_estimate="vtrace", epsilon=1e-6, behaviour="
 # they always did, and report what is wrong.
 class _FastCall:
     def __init__(self):
-        try:
-            from . import _fast_call
-        except ImportError as e:
-            raise RuntimeError("_fast_call.so cannot be loaded: build it with "
-                               "`python -m paper_1802_01561_amd.build`") from e
+        from . import _fast_call
+
         L = lib()
         self.call_targets, self.call_loss, self.call_head = _fast_call.targets, _fast_call.loss, _fast_call.head
         self.targets, self.loss, self.head = (
@@ -123,7 +121,7 @@ class _FastCall:
         self.device, self.stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
 
 
-_fast = None
+_fast = None  # the _FastCall, or False where it cannot be loaded
 _variants = {}  # settings -> (Variant, its address, log-probabilities, bfloat16 gradients)
 _MOST_VARIANTS = 64
 
@@ -134,8 +132,13 @@ def _fast_call(first) -> Optional[_FastCall]:
     if type(first) is not torch.Tensor or not first.is_cuda:
         return None
     if _fast is None:
-        _fast = _FastCall()
-    return _fast
+        try:
+            _fast = _FastCall()
+        except ImportError as e:  # not built, or built against another torch
+            _fast = False
+            warnings.warn(f"_fast_call.so cannot be loaded, calls take the slower Python path: {e}; build it "
+                          "with `python -m paper_1802_01561_amd.build`", RuntimeWarning, stacklevel=3)
+    return _fast or None
 
 
 def _fast_variant(*settings):

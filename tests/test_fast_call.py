@@ -2,6 +2,8 @@
 the same results bit for bit, the same errors, and everything unusual left to the
 Python path."""
 
+import warnings
+
 import numpy as np
 import pytest
 import torch
@@ -34,6 +36,28 @@ def test_host_tensors_are_declined():
     ws = _NoWorkspace()
     with pytest.raises(ValueError, match="GPU"):
         vt.vtrace_loss_grad(**x, out=out, workspace=ws)
+
+
+def _gpu_stand_in(monkeypatch):
+    """Stands in for a GPU tensor, which this machine may not have."""
+    x = type("Tensor", (), {"is_cuda": True})()
+    monkeypatch.setattr(binding.torch, "Tensor", type(x))
+    return x
+
+
+def test_without_the_extension_calls_take_the_python_path(monkeypatch):
+    """A tree with the library alone (or an extension built against another torch)
+    still runs every call; the loader's reason is told once."""
+    def fails(self):
+        raise ImportError("undefined symbol: of another torch")
+    x = _gpu_stand_in(monkeypatch)
+    monkeypatch.setattr(binding, "_fast", None)
+    monkeypatch.setattr(binding._FastCall, "__init__", fails)
+    with pytest.warns(RuntimeWarning, match="undefined symbol"):
+        assert binding._fast_call(x) is None
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        assert binding._fast_call(x) is None
 
 
 def test_variant_settings_are_bounded_and_exact():
