@@ -143,11 +143,11 @@ def _fast_call(first) -> Optional[_FastCall]:
 
 def _fast_variant(*settings):
     """_variant(*settings), made once per setting; None for an epsilon that is
-    not a plain float, whose value may change."""
+    not a plain float (whose value may change, or which has no hash)."""
+    if type(settings[2]) is not float:
+        return None
     known = _variants.get(settings)
     if known is None:
-        if type(settings[2]) is not float:
-            return None
         v = _variant(*settings)
         known = (v, ctypes.addressof(v), settings[3] == "log_probs", settings[5] is torch.bfloat16)
         if len(_variants) >= _MOST_VARIANTS:

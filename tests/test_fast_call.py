@@ -68,6 +68,7 @@ def test_variant_settings_are_bounded_and_exact():
     assert np.float32(v.epsilon) == np.float32(1e-3) and log_probs and bf16 and address
     assert binding._fast_variant(*key)[1] == address
     assert binding._fast_variant("epsilon", "vtrace", torch.tensor(1e-3), "logits", None, torch.float32) is None
+    assert binding._fast_variant("epsilon", "vtrace", np.array(1e-3), "logits", None, torch.float32) is None
     with pytest.raises(ValueError):
         binding._fast_variant("nonsense", "vtrace", 1e-6, "logits", None, torch.float32)
     for i in range(3 * binding._MOST_VARIANTS):
