@@ -88,9 +88,10 @@ hipError_t launch_tiled_a10_14(const StepArgs& a, LogitsType lt, int lanes, Mode
                                int64_t* num_workgroups, bool allow_multi);
 hipError_t launch_tiled_a15_20(const StepArgs& a, LogitsType lt, int lanes, Mode mode, hipStream_t s,
                                int64_t* num_workgroups, bool allow_multi);
-// The row-split kernel covers kTiledMaxActions < A <= kRowsMaxActions.
+// The row-split kernel covers kTiledMaxActions < A <= kRowsMaxActions, but for short
+// unrolls of many lanes.
 constexpr int64_t kRowsMaxActions = 256;
-bool rows_supported(const StepArgs& a, LogitsType lt);
+bool rows_supported(const StepArgs& a, LogitsType lt, Mode mode);
 hipError_t launch_rows(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s, int64_t* num_workgroups);
 hipError_t launch_gather(int64_t T, int64_t B, int64_t A, LogitsType lt, const void* target,
                          const void* behaviour, const int32_t* actions, void* gathered,

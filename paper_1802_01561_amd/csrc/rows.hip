@@ -38,8 +38,10 @@ namespace {
 constexpr int kRowsThreads = 256;
 constexpr int kRowsPerGroup = 4;
 // Workgroups of a launch; larger batches loop over lanes, so that the loss
-// ticket is taken a bounded number of times.
-constexpr int64_t kRowsMaxWorkgroups = 4096;
+// ticket, which takes about 10 ns a workgroup, is taken a bounded number of times
+// (loss, B = 4096: T = 1, A = 21 59 -> 40 us, T = 100, A = 48 116 -> 108 with 2048
+// in place of 4096; targets, which take none, 16 and 59 us with 4096, 16 and 62).
+constexpr int64_t kRowsMaxWorkgroups = 4096, kRowsMaxLossWorkgroups = 2048;
 
 // Butterfly moves over the G threads of a group: within a DPP row of 16 by
 // quad permutes and mirrors (every thread ends with the same bits: each stage
@@ -398,7 +400,8 @@ __global__ __launch_bounds__(kRowsThreads, K == 2 ? 3 : 2) void rows_kernel(Step
 
 template <int G, int K, typename In>
 hipError_t launch_rows_shape(const StepArgs& a, Mode mode, hipStream_t st, int64_t* nwg) {
-  *nwg = a.B < kRowsMaxWorkgroups ? a.B : kRowsMaxWorkgroups;
+  const int64_t most = mode == Mode::LossGrad ? kRowsMaxLossWorkgroups : kRowsMaxWorkgroups;
+  *nwg = a.B < most ? a.B : most;
   const dim3 grid(static_cast<unsigned>(*nwg)), block(kRowsThreads);
   if (mode != Mode::LossGrad)
     hipLaunchKernelGGL((rows_kernel<G, K, In, false, false>), grid, block, 0, st, a);
@@ -419,16 +422,34 @@ hipError_t launch_rows_typed(const StepArgs& a, Mode mode, hipStream_t st, int64
   return launch_rows_shape<64, 4, In>(a, mode, st, nwg);
 }
 
+// A workgroup of this kernel takes a lane's chunk whole however short the unroll
+// is; one thread per lane takes its A T logits one after another, and from a few
+// thousand lanes on fills the chip with them.  That is faster up to the A T below
+// (us, row-split / one thread per lane; loss: B = 512, T = 1, A = 21 14 / 16;
+// B = 1024, A = 21, T = 1 20 / 16 and T = 2 20 / 28; B = 4096, A = 21, T = 2 40 / 28
+// and T = 4 40 / 53, A = 48, T = 1 46 / 35; B = 16384, T = 8, A = 21 104 / 109, T = 2,
+// A = 48 127 / 68 and T = 4 128 / 132; B = 60000, T = 1, A = 21 334 / 36, T = 20 450 /
+// 432 and A = 48, T = 8 438 / 549, with bfloat16 411 / 312 and 499 / 409.  Targets: B = 1024, T = 1, A = 21 6 / 8; B = 2048
+// 10 / 8; B = 4096, T = 2 17 / 15, A = 48, T = 1 19 / 18; B = 16384, A = 21, T = 4 53 /
+// 27 and T = 8 54 / 57; B = 60000, A = 48, T = 4 209 / 193 and A = 21, T = 8 192 / 109).
+bool one_thread_per_lane(const StepArgs& a, LogitsType lt, Mode mode) {
+  if (a.T > 1000) return false;
+  const int64_t n = a.A * a.T;
+  if (mode != Mode::LossGrad) return a.B >= 2048 && n <= 220 && n * 90 < a.B;
+  return a.B >= 1024 && (10 * n * n < (a.B < 8192 ? 11 : 22) * a.B || (lt == LogitsType::BF16 && n * 110 < a.B));
+}
+
 }  // namespace
 
 // 64 rows of an array (the longest chunk) must fit the kernel's 32-bit byte
 // offsets: 64 B A 4 < 2^32.
-bool rows_supported(const StepArgs& a, LogitsType) {
-  return a.A > kTiledMaxActions && a.A <= kRowsMaxActions && a.B * a.A < (int64_t(1) << 24);
+bool rows_supported(const StepArgs& a, LogitsType lt, Mode mode) {
+  return a.A > kTiledMaxActions && a.A <= kRowsMaxActions && a.B * a.A < (int64_t(1) << 24) &&
+         !one_thread_per_lane(a, lt, mode);
 }
 
 hipError_t launch_rows(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t st, int64_t* num_workgroups) {
-  if (!rows_supported(a, lt)) return hipErrorNotSupported;
+  if (!rows_supported(a, lt, mode)) return hipErrorNotSupported;
   if (lt == LogitsType::F32) return launch_rows_typed<float>(a, mode, st, num_workgroups);
   return launch_rows_typed<uint16_t>(a, mode, st, num_workgroups);
 }

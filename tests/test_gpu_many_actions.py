@@ -11,9 +11,10 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import paper_1802_01561_amd as vt
-from gpu_util import log_case, np_out, require_gpu, to_device
-from synth import Params, make_random
+from gpu_util import assert_close, log_case, np_out, oracle_args, require_gpu, to_device
+from synth import Params, make_random, subset_lanes
 from test_gpu_variants import check_io_variant
 
 pytestmark = pytest.mark.gpu
@@ -59,6 +60,22 @@ def test_more_lanes_than_workgroups():
     tr = make_random(9, B, 22, 8300, noise_std=1.0, end_prob=0.05)
     log_case("rows, lanes beyond the workgroup count")
     check_io_variant(tr, Params(1.0, 1.0, 1.0), lanes=[0, 1, 4094, 4095, 4096, 4097, B - 1])
+
+
+@pytest.mark.parametrize("T,B,A", [(1, 1023, 21), (1, 1024, 21), (2, 1024, 21), (1, 2049, 22), (3, 4098, 21),
+                                   (7, 8191, 22), (1, 8200, 113), (4, 16384, 40), (1, 20000, 220)])
+def test_short_unrolls_of_many_lanes(T, B, A):
+    """Both sides of the rule that gives short unrolls one thread per lane, and
+    lanes beyond either kernel's workgroups."""
+    tr = make_random(T, B, A, 8500 + A + T, noise_std=1.0, end_prob=0.05)
+    log_case(f"rows or one thread per lane, T={T} B={B} A={A}")
+    lanes = sorted({0, 1, 63, 64, *range(B - 3, B), *(i for i in (2047, 2048, 4095, 4096) if i < B)})
+    check_io_variant(tr, Params(1.0, 1.0, 1.0), lanes=lanes)
+    vs, pg = vt.vtrace_targets(**to_device(tr))
+    sub = subset_lanes(tr, lanes)
+    o = oracle.vtrace(*oracle_args(sub), 1.0, 1.0, 1.0)
+    assert_close("targets.vs", np_out(vs)[:, lanes], o.vs)
+    assert_close("targets.pg_advantages", np_out(pg)[:, lanes], o.pg_advantages)
 
 
 def test_bad_values_stay_in_their_lane():
