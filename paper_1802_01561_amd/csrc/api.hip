@@ -178,7 +178,7 @@ vtrace_status launch(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s)
   rule.time_parallel = k == Kernel::Wide && a.T <= vtrace::kMaxChunkSteps;
   if (k == Kernel::LaneSerial)
     e = vtrace::launch_lane_serial(a, lt, mode, s, &nwg);
-  else if (vtrace::tiled_supported(a, lt))
+  else if (vtrace::tiled_supported(a, lt, mode))
     e = vtrace::launch_tiled(a, lt, mode, s, &nwg, rule);
   else if (vtrace::rows_supported(a, lt, mode))
     e = vtrace::launch_rows(a, lt, mode, s, &nwg);

@@ -59,11 +59,13 @@ enum class Mode { Targets, LossGrad };
 // Kernel launchers.  They return the HIP status of the launch.
 hipError_t launch_lane_serial(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t s,
                               int64_t* num_workgroups);
-bool tiled_supported(const StepArgs& a, LogitsType lt);
+bool tiled_supported(const StepArgs& a, LogitsType lt, Mode mode);
 // The tiled kernel covers 2 <= A <= kTiledMaxActions (beyond, its per-thread
-// prefetch no longer fits the registers of two waves per SIMD) and batches whose
-// 16 time rows its 32-bit offsets reach.
+// prefetch no longer fits the registers of two waves per SIMD), but for short unrolls
+// of the very widest batches; and fewer lanes than give a launch 2^32 threads at 16
+// a lane.
 constexpr int64_t kTiledMaxActions = 20;
+constexpr int64_t kTiledMaxLanes = int64_t(1) << 28;
 // Which tile shapes a call may take.
 struct TileRule {
   bool multi = true;      // the multi-tile walk

@@ -5,8 +5,24 @@
 
 namespace vtrace {
 
-bool tiled_supported(const StepArgs& a, LogitsType) {
-  return a.A >= 2 && a.A <= kTiledMaxActions && rows_fit(a, kL);
+// Time rows that 32-bit offsets do not reach 16 of: one thread per lane has millions
+// of lanes to fill the chip with, and needs no ticket per 16 lanes; tiles win once
+// a lane's logits are many (ms, tiles / one thread per lane; rows of 1.05 * 2^26
+// elements, loss: A = 18, T = 4 3.9 / 5.4, with bfloat16 logits 3.8 / 3.4, T = 16 4.7 /
+// 20.8; A = 9, T = 4 6.4 / 3.5, T = 16 7.7 / 11.8; A = 6, T = 16 10.2 / 11.8; A = 2,
+// T = 20 29.6 / 23.8.  Targets: A = 18, T = 4 1.1 / 3.5; A = 6, T = 4 1.45 / 1.47, with
+// bfloat16 1.33 / 1.21; A = 9, T = 4 1.13 / 1.13 with bfloat16; A = 2, T = 20 12.9 /
+// 10.1).
+bool far_tiles_faster(const StepArgs& a, LogitsType lt, Mode mode) {
+  const bool f32 = lt == LogitsType::F32;
+  if (a.T >= 128) return mode == Mode::LossGrad || a.A >= 4;
+  if (mode == Mode::LossGrad) return a.A * a.T >= (f32 ? 72 : 90);
+  return a.A >= 4 && a.A * a.T >= (f32 ? 24 : 36);
+}
+
+bool tiled_supported(const StepArgs& a, LogitsType lt, Mode mode) {
+  return a.A >= 2 && a.A <= kTiledMaxActions &&
+         (rows_fit(a, kL) || (a.B < kTiledMaxLanes && far_tiles_faster(a, lt, mode)));
 }
 
 // Tiles of 256 threads: `lanes` lanes, 256 / lanes steps per chunk.
@@ -93,15 +109,15 @@ hipError_t launch_tiled(const StepArgs& a, LogitsType lt, Mode mode, hipStream_t
       if (launched) return err;
     }
     if (rule.shapes) lanes = tile_lanes(a, cus, rule.one_chunk);
-    if (lanes == 16 && wide_tiles(a, lt, cus, a.T <= 16 || !rule.shapes)) {
+    if (lanes == 16 && rows_fit(a, kL) && wide_tiles(a, lt, cus, a.T <= 16 || !rule.shapes)) {
       if (a.A == 9) return launch_shape<9, 32, float>(a, mode, st, num_workgroups, rule.multi);
       return launch_shape<18, 32, uint16_t>(a, mode, st, num_workgroups, rule.multi);
     }
   }
-  while (lanes > a.B || !rows_fit(a, kTileThreads / lanes)) {
-    // (tiled_supported: 16 lanes fit.)
+  // (Such rows are of 2^26 elements or more: more than 16 lanes.)
+  if (!rows_fit(a, kL)) lanes = kFarLanes;
+  while (lanes != kFarLanes && (lanes > a.B || !rows_fit(a, kTileThreads / lanes)))
     lanes = lanes > a.B ? lanes / 2 : lanes * 2;
-  }
   if (a.A == 18) return launch_any<18>(a, lt, lanes, mode, st, num_workgroups, rule.multi);
   if (a.A == 9) return launch_any<9>(a, lt, lanes, mode, st, num_workgroups, rule.multi);
   // The other action counts are instantiated in three more files, which

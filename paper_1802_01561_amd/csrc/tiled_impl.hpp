@@ -52,7 +52,7 @@ namespace vtrace {
 namespace {
 
 constexpr int kL = 16;  // default steps per chunk
-
+constexpr int kFarLanes = 0;  // in place of a tile's lanes: the kernels for rows far apart
 
 // DPP row_shr:(L-1): lane i of a 16-lane row reads lane i-L+1, so the last
 // lane of every aligned L-lane segment reads the segment's first (L = 16 is
@@ -252,7 +252,8 @@ __device__ __forceinline__ void workgroup_losses(const StepArgs& a, int64_t b, i
 // tile_stride, i < ntiles, one after another as one loop over their chunks, so
 // that the prefetch runs across tile boundaries; each lane's loss totals are
 // then added to acc[3 * lane], a slot only the lane's step-0 thread touches.
-template <int A_, int LANES, typename In, int L, bool kGrad, bool kPrecise, bool kMulti, int kPlain>
+// kFar: L rows of an array lie further apart than 32-bit offsets reach.
+template <int A_, int LANES, typename In, int L, bool kGrad, bool kPrecise, bool kMulti, int kPlain, bool kFar>
 __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t first_tile,
                                            int64_t tile_stride, int64_t ntiles, Carry& cy,
                                            double* acc, WaveMap* maps, double* red) {
@@ -311,11 +312,12 @@ __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t 
   // Addresses are a wave-uniform base (the chunk's row 0 at the tile's first
   // lane, in scalar registers) plus a per-thread 32-bit offset, the form of the
   // loads' and stores' scalar-base addressing; the launcher checks that L rows
-  // of every array fit 32-bit offsets.
+  // of every array fit 32-bit offsets, or takes kFar and 64-bit ones.
+  using Off = std::conditional_t<kFar, uint64_t, uint32_t>;
   typedef GlobalVec<S::IN_VB, sizeof(In)> GlobalIn;
-  const uint32_t in_row32 = static_cast<uint32_t>(in_row);
-  const uint32_t out_row32 = static_cast<uint32_t>(out_row);
-  const uint32_t B32 = static_cast<uint32_t>(B);
+  const Off in_row_off = static_cast<Off>(in_row);
+  const Off out_row_off = static_cast<Off>(out_row);
+  const Off b_off = static_cast<Off>(B);
   auto prefetch = [&](int64_t tile, int k) {
     const int64_t b0 = first_lane(tile);
     const int64_t t0 = T - static_cast<int64_t>(k + 1) * L;
@@ -337,7 +339,7 @@ __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t 
         int r = g / S::IN_ROW;
         const int c = g % S::IN_ROW;
         r = r < neg ? neg : r;
-        const uint32_t off = static_cast<uint32_t>(r) * in_row32 + static_cast<uint32_t>(c * S::IN_VB);
+        const Off off = static_cast<Off>(r) * in_row_off + static_cast<Off>(c * S::IN_VB);
         const auto src = reinterpret_cast<gptr<const GlobalIn>>((is_y ? yg : zg) + off);
         if constexpr (S::kStream)
           pre[i] = __builtin_nontemporal_load(src);
@@ -345,15 +347,15 @@ __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t 
           pre[i] = *src;
       }
     });
-    const uint32_t off = static_cast<uint32_t>(s < neg ? neg : s) * B32 + static_cast<uint32_t>(lane_local);
+    const Off off = static_cast<Off>(s < neg ? neg : s) * b_off + static_cast<Off>(lane_local);
     p_act = offset_elems(a.actions, row0)[off];
     p_r = offset_elems(a.rewards, row0)[off];
     p_g = offset_elems(a.discounts, row0)[off];
     p_V = offset_elems(a.values, row0)[off];
     if constexpr (L > kWave) {  // V(x_{t+1}), which a wave's last thread cannot take from a neighbour
       const int sn = s + 1 < L ? s + 1 : s;
-      p_Vn = offset_elems(a.values, row0)[static_cast<uint32_t>(sn < neg ? neg : sn) * B32 +
-                                          static_cast<uint32_t>(lane_local)];
+      p_Vn = offset_elems(a.values, row0)[static_cast<Off>(sn < neg ? neg : sn) * b_off +
+                                          static_cast<Off>(lane_local)];
     }
     // (Cleared first: a value kept where nothing is loaded would make the
     // compiler wait for the loads just issued.)
@@ -389,9 +391,9 @@ __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t 
     const int64_t t0 = T - static_cast<int64_t>(k + 1) * L;
     const int64_t t = t0 + s;
     const bool step_ok = t >= 0;
-    // [T,B] element (t, b) as the chunk's uniform row 0 plus a 32-bit offset.
+    // [T,B] element (t, b) as the chunk's uniform row 0 plus an offset.
     const int64_t row0 = t0 * B + b0;
-    const uint32_t soff = static_cast<uint32_t>(s) * B32 + static_cast<uint32_t>(lane_local);
+    const Off soff = static_cast<Off>(s) * b_off + static_cast<Off>(lane_local);
 
     // Every thread is past the previous chunk's row reads: the gradient
     // kernels passed their staging barrier after them; the targets-only
@@ -663,7 +665,7 @@ __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t 
             const int rr = f / S::OUT_ROW, cc = f % S::OUT_ROW;
             if (rr >= neg) {
               const auto dst = reinterpret_cast<gptr<GlobalOut>>(
-                  dgr + (static_cast<uint32_t>(rr) * out_row32 + static_cast<uint32_t>(cc * S::OUT_VB)));
+                  dgr + (static_cast<Off>(rr) * out_row_off + static_cast<Off>(cc * S::OUT_VB)));
               if constexpr (S::kStream)
                 __builtin_nontemporal_store(lds_g[rr * S::OUT_PITCH_V + cc], dst);
               else
@@ -701,7 +703,7 @@ __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t 
               }
             }
             const auto dst = reinterpret_cast<gptr<GlobalOut>>(
-                dgr + (static_cast<uint32_t>(rr) * out_row32 + static_cast<uint32_t>(cc * S::OUT16_VB)));
+                dgr + (static_cast<Off>(rr) * out_row_off + static_cast<Off>(cc * S::OUT16_VB)));
             if constexpr (S::kStream)
               __builtin_nontemporal_store(pk, dst);
             else
@@ -762,7 +764,8 @@ __device__ __forceinline__ int64_t first_tile_of_workgroup() {
 // workgroups whenever a slot frees, and leave the chip partly idle at the end.
 // The fp64 ratio mode with A > 18 is asked for two waves per SIMD explicitly:
 // left to itself the compiler gives A = 19 two registers more than fit.
-template <int A_, int LANES, typename In, int L, bool kGrad, bool kPrecise, bool kMulti, int kPlain = kGeneralCall>
+template <int A_, int LANES, typename In, int L, bool kGrad, bool kPrecise, bool kMulti, int kPlain = kGeneralCall,
+          bool kFar = false>
 __global__ __launch_bounds__(LANES* L, (kPrecise && A_ >= 18) ? 2 : 1) void tiled_kernel(
     StepArgs a, int64_t tiles_per_wg) {
   using S = Tile<A_, LANES, In, L>;
@@ -778,8 +781,8 @@ __global__ __launch_bounds__(LANES* L, (kPrecise && A_ >= 18) ? 2 : 1) void tile
     __shared__ double acc[3 * LANES];  // per-lane loss sums over the workgroup's tiles
     if (s == 0) acc[3 * lane_local + 0] = acc[3 * lane_local + 1] = acc[3 * lane_local + 2] = 0.0;
     Carry cy{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    chunk_walk<A_, LANES, In, L, kGrad, kPrecise, true, kPlain>(a, lds, first_tile_of_workgroup<LANES>(),
-                                                                gridDim.x, tiles_per_wg, cy, acc, maps, red_scratch);
+    chunk_walk<A_, LANES, In, L, kGrad, kPrecise, true, kPlain, kFar>(
+        a, lds, first_tile_of_workgroup<LANES>(), gridDim.x, tiles_per_wg, cy, acc, maps, red_scratch);
     if constexpr (kGrad) {
       double pg = 0.0, base = 0.0, ent = 0.0;
       if (s == 0) {
@@ -796,7 +799,8 @@ __global__ __launch_bounds__(LANES* L, (kPrecise && A_ >= 18) ? 2 : 1) void tile
     const int64_t b = b0 + lane_local;
     const double boot = static_cast<double>(a.bootstrap_value[b]);
     Carry cy{boot, boot, 0.0, 0.0, 0.0, 0.0};
-    chunk_walk<A_, LANES, In, L, kGrad, kPrecise, false, kPlain>(a, lds, tile, 0, 1, cy, nullptr, maps, red_scratch);
+    chunk_walk<A_, LANES, In, L, kGrad, kPrecise, false, kPlain, kFar>(a, lds, tile, 0, 1, cy, nullptr, maps,
+                                                                       red_scratch);
 
     if constexpr (kGrad) {
       if constexpr (L >= 32) {
@@ -1105,7 +1109,29 @@ bool launch_long_loss(const StepArgs& a, hipStream_t st, int64_t* nwg, hipError_
   return launch_long_loss<A_, In, Shapes...>(a, st, nwg, err, cus);
 }
 
-// Launches tiles of `lanes` lanes, 256 / lanes steps per chunk.
+// Batches whose 16 time rows 32-bit offsets do not reach: tiles of 16 lanes by 16
+// steps again, in the general kernels alone.  (T = 16, 3914624 lanes, A = 18: loss
+// 4.7 ms, 20.8 with one thread per lane; targets 2.2 against 18.7.)
+template <int A_, typename In>
+hipError_t launch_far(const StepArgs& a, Mode mode, hipStream_t st, int64_t* nwg) {
+  constexpr int LANES = 16;
+  if (a.B < LANES || a.B >= kTiledMaxLanes) return hipErrorInvalidValue;
+  *nwg = (a.B + LANES - 1) / LANES;
+  const dim3 grid(static_cast<unsigned>(*nwg)), block(LANES * kL);
+  if (mode == Mode::LossGrad)
+    hipLaunchKernelGGL((tiled_kernel<A_, LANES, In, kL, true, true, false, kGeneralCall, true>), grid, block, 0, st, a,
+                       int64_t(1));
+  else if (precise_row_sums(a, false))
+    hipLaunchKernelGGL((tiled_kernel<A_, LANES, In, kL, false, true, false, kGeneralCall, true>), grid, block, 0, st, a,
+                       int64_t(1));
+  else
+    hipLaunchKernelGGL((tiled_kernel<A_, LANES, In, kL, false, false, false, kGeneralCall, true>), grid, block, 0, st, a,
+                       int64_t(1));
+  return hipGetLastError();
+}
+
+// Launches tiles of `lanes` lanes, 256 / lanes steps per chunk (kFarLanes: those
+// for rows far apart).
 template <int A_, typename In>
 hipError_t launch_lanes(int lanes, const StepArgs& a, Mode mode, hipStream_t st, int64_t* nwg, bool allow_multi) {
   switch (lanes) {
@@ -1114,6 +1140,7 @@ hipError_t launch_lanes(int lanes, const StepArgs& a, Mode mode, hipStream_t st,
     case 4: return launch_shape<A_, 4, In, 64>(a, mode, st, nwg, false);
     case 2: return launch_shape<A_, 2, In, 128>(a, mode, st, nwg, false);
     case 1: return launch_shape<A_, 1, In, 256>(a, mode, st, nwg, false);
+    case kFarLanes: return launch_far<A_, In>(a, mode, st, nwg);
     default: return hipErrorInvalidValue;
   }
 }

@@ -90,3 +90,43 @@ def test_unclipped_weights_and_replays(T, B, A):
         for name, x, y in zip(out._fields, out, eager):
             assert torch.equal(x, y), name
         run_loss_grad(dev, Params(1.0, 1.0, 1.0), workspace=ws)  # eager work between replays
+
+
+@pytest.mark.parametrize("T,B,A,bf16,variant", [
+    (18, 2 ** 22 + 37, 18, False, {}),
+    (5, 2 ** 26 // 20 + 3, 20, True, dict(grad_dtype=torch.bfloat16)),
+    (37, 2 ** 25 + 1, 2, False, {}),  # the loss call tiled, the targets one thread per lane
+    (8, 2 ** 23 + 5, 9, False, dict(behaviour="log_probs", reward_transform="clip")),
+    (2, 2 ** 23 + 5, 9, True, {})])  # one thread per lane
+def test_time_rows_beyond_32_bit_offsets(T, B, A, bf16, variant):
+    """Time rows of 2^26 elements or more, 16 of which 32-bit byte offsets do not
+    reach: chosen lanes against the oracle, the totals against the lane losses."""
+    log_case(f"far rows T={T} B={B} A={A} bf16={bf16} {variant}")
+    g = torch.Generator(device="cuda").manual_seed(9300 + A)
+    f = lambda *s: torch.randn(s, generator=g, device="cuda")  # noqa: E731
+    log_probs = variant.get("behaviour") == "log_probs"
+    x = dict(target_logits=f(T, B, A), behaviour_logits=-f(T, B).abs() - 0.5 if log_probs else f(T, B, A),
+             actions=torch.randint(0, A, (T, B), generator=g, device="cuda", dtype=torch.int32), rewards=f(T, B),
+             discounts=torch.where(f(T, B) > 1.5, 0.0, 0.99), values=f(T, B), bootstrap_value=f(B))
+    if bf16:
+        x.update(target_logits=x["target_logits"].bfloat16(), behaviour_logits=x["behaviour_logits"].bfloat16())
+    lanes = sorted({0, 1, 15, 16, B // 2, B // 3, *range(B - 20, B)})
+    at = torch.tensor(lanes, device="cuda")
+    p = call_params(Params(1.0, 1.0, 0.9))
+    out = run_loss_grad(x, p, **variant)
+    vs, pg = vt.vtrace_targets(**x, rho_bar=p.rho_bar, c_bar=p.c_bar, lam=p.lam,
+                               **{k: v for k, v in variant.items() if k != "grad_dtype"})
+    pick = lambda t: t.index_select(0 if t.dim() == 1 else 1, at).cpu()  # noqa: E731
+    args = [pick(t).float().numpy() if t.is_floating_point() else pick(t).numpy() for t in x.values()]
+    o = oracle.loss_and_grads(*args, p.rho_bar, p.c_bar, p.lam, p.baseline_cost, p.entropy_cost,
+                              **{k: v for k, v in variant.items() if k != "grad_dtype"})
+    rel = 2.0 ** -8 if "grad_dtype" in variant else 1e-4
+    for name, t, e in (("vs", out.vs, o.vs), ("pg_advantages", out.pg_advantages, o.pg_advantages),
+                       ("d_values", out.d_values, o.d_values), ("targets.vs", vs, o.vs),
+                       ("targets.pg_advantages", pg, o.pg_advantages)):
+        assert_close(name, pick(t).numpy(), e)
+    assert_close("d_logits", pick(out.d_logits).float().numpy(), o.d_logits, rtol=rel)
+    assert_close("lane_losses", out.lane_losses[at].cpu().numpy(), o.lane_losses)
+    sums = out.lane_losses.double().sum(0).cpu().numpy()
+    rss = out.lane_losses.double().square().sum(0).sqrt().cpu().numpy()
+    assert np.all(np.abs(np_out(out.losses)[1:] - sums) <= 1e-5 * rss + 1e-4 * np.abs(sums))
