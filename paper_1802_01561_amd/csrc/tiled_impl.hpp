@@ -248,7 +248,7 @@ __device__ __forceinline__ void workgroup_losses(const StepArgs& a, int64_t b, i
 }
 
 // Walks one tile (kMulti false: `tile`, with the carry cy set up by the
-// caller), or (kMulti true, L <= 32, whole tiles only) the tiles first_tile + i *
+// caller), or (kMulti true, L <= 16, whole tiles only) the tiles first_tile + i *
 // tile_stride, i < ntiles, one after another as one loop over their chunks, so
 // that the prefetch runs across tile boundaries; each lane's loss totals are
 // then added to acc[3 * lane], a slot only the lane's step-0 thread touches.
@@ -257,7 +257,7 @@ template <int A_, int LANES, typename In, int L, bool kGrad, bool kPrecise, bool
 __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t first_tile,
                                            int64_t tile_stride, int64_t ntiles, Carry& cy,
                                            double* acc, WaveMap* maps, double* red) {
-  static_assert(!kMulti || L <= 32, "the multi-tile walk takes lanes within one wave");
+  static_assert(!kMulti || L <= 16, "the multi-tile walk takes lanes within one DPP row");
   using S = Tile<A_, LANES, In, L>;
   constexpr int NT = S::NT;
   typedef typename S::InVec InVec;
@@ -899,7 +899,7 @@ int compute_units() {
 // slower.
 template <int A_, int LANES, typename In, int L, bool kGrad, bool kPrecise, int kPlain = kGeneralCall>
 int64_t launch_kernel(const StepArgs& a, hipStream_t st, int64_t tiles, bool allow_multi) {
-  if constexpr (!kPrecise && L <= 32) {
+  if constexpr (!kPrecise && L <= 16) {
     const int per_cu = allow_multi && a.B % LANES == 0 ? multi_workgroups_per_cu<A_, LANES, In, L, kGrad>() : 0;
     if (per_cu >= 2) {
       const int64_t resident = static_cast<int64_t>(per_cu) * compute_units();

@@ -613,11 +613,12 @@ def test_long_run_tile_shapes_short_unrolls(lanes_per_cu, T, monkeypatch):
 @pytest.mark.parametrize("T,B,A,bf16", [(512, 4096, 18, False), (513, 4096, 18, False), (544, 4091, 18, True),
                                          (1000, 2048, 18, False), (543, 1000, 18, True)])
 def test_two_row_chunks(T, B, A, bf16):
-    """Batches of at most 16 lanes per CU with A = 18 and T >= 512 take
-    32-step chunks (two lanes per wave, each on two DPP rows joined by one
-    cross-row step of the scan): whole chunks, one step more than whole
-    chunks, a lane tile cut short (element path), bf16 logits, every output
-    against the oracle, for the loss call and the targets-only call."""
+    """Long unrolls of at most 16 lanes per CU take tiles of 8 lanes by 32 steps
+    (two lanes per wave, each on two DPP rows joined by one cross-row step of
+    the scan), or fewer lanes by more steps: whole chunks, one step more than
+    whole chunks, a last lane tile moved back over its neighbour, bf16 logits,
+    every output against the oracle, for the loss call and the targets-only
+    call."""
     tr = make_random(T, B, A, 5100 + T + B, noise_std=1.0, end_prob=0.02, bf16=bf16)
     dev = to_device(tr)
     p = PARAM_SETS[4][1] if T == 513 else PARAM_SETS[4][0]
@@ -717,8 +718,8 @@ def test_wide_kernel_shapes(T, B, A, monkeypatch):
 def test_offsets_beyond_four_gib(B):
     """Logit tensors larger than 2^32 bytes (T=64, B=2^20+8 or 2^20, A=18:
     4.8 GB each): byte offsets need more than 32 bits, signed or not.  With
-    2^20 + 8 lanes rows stay 16-byte aligned, so all but the last, ragged
-    workgroup take the vector path of the 16-step tiles; 2^20 lanes are a whole
+    2^20 + 8 lanes the 16-step tiles run it, the last one moved back by half a
+    tile; 2^20 lanes are a whole
     number of generations of the 64 x 4 long-run tiles, which take the
     multi-tile walk (on a 256-CU part).  The oracle checks lanes spread over
     the batch, including the last ones, whose elements lie beyond 2^32 bytes."""
