@@ -20,7 +20,7 @@ struct RowStats {
   float H;            // entropy of pi
   float one_minus_pa; // 1 - pi(a|x), formed without cancellation
   float e_a;          // exp(z_a - m_z)
-  float mz;
+  float mz, za;       // the maximum and the taken action's logit (precise mode: of the row as brought within)
 };
 
 // Maximum of a row of logits, NaN if any logit is NaN (the IEEE maximum,
@@ -90,25 +90,10 @@ __device__ __forceinline__ bool row_plain(const float (&v)[A_], float m) {
   return mn - m > -kMostBelow && __builtin_fabsf(m) < kMostMaximum;
 }
 
-// Brings any row with a finite maximum within those bounds without changing its
-// softmax, and returns the new maximum: logits more than 1e4 below it are raised
-// to there, where their exponentials are 0 all the same, and a row with a large
-// maximum is shifted by it (a float32 difference: exact for logits within a factor
-// of two of it, and the others' exponentials are 0).  -inf logits become zero-probability actions;
-// *any_inf tells.
-template <int A_>
-__device__ __forceinline__ float bring_within(float (&v)[A_], float m, bool* any_inf) {
-  const float shift = __builtin_fabsf(m) < kMostMaximum ? 0.0f : m;
-  const float least = (m - shift) - 1e4f;
-  bool inf = false;
-#pragma unroll
-  for (int j = 0; j < A_; ++j) {
-    inf = inf || v[j] == -INFINITY;
-    v[j] = fmaxf(v[j] - shift, least);
-  }
-  *any_inf = inf;
-  return m - shift;
-}
+// What such a row's logits are shifted by: a large maximum, so that differences from
+// it are float32 ones, exact for logits within a factor of two of it (the others'
+// exponentials are 0); 0 for rows with no such maximum.
+__device__ __forceinline__ float row_shift(float m) { return __builtin_fabsf(m) < kMostMaximum ? 0.0f : m; }
 
 // The rest of a target row's precise statistics (all of RowStats but the
 // ratio) from its maximum mz, dza = z_a - m_z, the sums sz = sum_j e_j and
@@ -134,17 +119,18 @@ __device__ __forceinline__ void finish_target_stats(RowStats& st, float mz, doub
   st.dza = dza;
 }
 
-// A row beyond the plain terms' bounds is brought within them and written back, so
-// that later readers see the logits that go with st.mz.  Its -inf logits, as
-// inputs whose logarithm the entropy takes, make the entropy and with it the
-// gradient row NaN.  (The terms stand in both branches: behind one that changes
-// the row, a single copy took T = 1000, B = 512, A = 18 40 -> 42 us.)
-template <int A_, typename In>
+// In a wave with a row that is not plain every row takes the clamped terms (a plain
+// row's are the same bits), of its logits less their shift.  For the gradient such a
+// row's logits are then changed to ones with the same softmax, shifted and with
+// masked ones raised to 1e4 below the maximum, where their exponentials are 0 all the
+// same: in zo or, for a caller that reads the row again (kReread), in place, to go
+// with st.mz and st.za.  (-inf logits make the entropy NaN, and with it the row.)
+template <int A_, bool kGrad, bool kReread, typename In>
 __device__ __forceinline__ RowStats target_row_stats(In* zr, int act_c, float* e, float* zo) {
   RowStats st;
   const float za = logit_to_float(zr[act_c]);
   float z[A_];
-  const float m = read_row_max<A_>(zr, z);
+  float m = read_row_max<A_>(zr, z);
   if (zo != nullptr) {
 #pragma unroll
     for (int j = 0; j < A_; ++j) zo[j] = z[j];
@@ -153,39 +139,47 @@ __device__ __forceinline__ RowStats target_row_stats(In* zr, int act_c, float* e
   // drop the first addition.
   double sz = -0.0;
   double ed = -0.0;  // sum_j e_j (z_j - m_z) log2 e, for the entropy
-  double ea;
-  auto terms = [&](const float (&x)[A_], float mx, float xa) {
-    const double mxl = static_cast<double>(mx) * kLog2eF64;
+  double ea, dza;
+  auto terms = [&](auto careful, float shift) {
+    constexpr bool kCareful = decltype(careful)::value;
+    auto shifted = [&](float x) { return kCareful ? x - shift : x; };
+    const double ml = static_cast<double>(shifted(m)) * kLog2eF64;
     static_for<A_>([&](auto J) {
       constexpr int j = decltype(J)::value;
-      const double xj = fma(static_cast<double>(x[j]), kLog2eF64, -mxl);
-      const double ej = exp2_f64_term<false>(xj);
+      const double xj = fma(static_cast<double>(shifted(z[j])), kLog2eF64, -ml);
+      const double ej = exp2_f64_term<kCareful>(xj);
       sz += ej;
       e[j] = static_cast<float>(ej);
       ed = fma(ej, xj, ed);
       asm volatile("" : "+v"(sz), "+v"(ed));
     });
-    ea = exp2_f64_term<false>(fma(static_cast<double>(xa), kLog2eF64, -mxl));
+    ea = exp2_f64_term<kCareful>(fma(static_cast<double>(shifted(za)), kLog2eF64, -ml));
+    dza = static_cast<double>(za) - static_cast<double>(m);  // exact
   };
-  float mz = m;
-  bool any_inf = false;
-  if (row_plain<A_>(z, m)) {
-    terms(z, m, za);
+  st.za = za;
+  const bool plain = row_plain<A_>(z, m);
+  if (__all(plain)) {
+    terms(std::false_type{}, 0.0f);
   } else {
-    mz = bring_within<A_>(z, m, &any_inf);
+    const float shift = row_shift(m);
+    terms(std::true_type{}, shift);
+    m -= shift;
+    if (kGrad && !plain) {
 #pragma unroll
-    for (int j = 0; j < A_; ++j) {
-      if (zo != nullptr) zo[j] = z[j];
-      if constexpr (std::is_same_v<In, float>)
-        zr[j] = z[j];
-      else
-        zr[j] = to_bf16(z[j]);
+      for (int j = 0; j < A_; ++j) {
+        const float x = fmaxf(z[j] - shift, m - 1e4f);
+        st.za = j == act_c ? x : st.za;
+        if (zo != nullptr) zo[j] = x;
+        if constexpr (kReread) {
+          if constexpr (std::is_same_v<In, float>)
+            zr[j] = x;
+          else
+            zr[j] = to_bf16(x);
+        }
+      }
     }
-    terms(z, mz, logit_to_float(zr[act_c]));
   }
-  const double dza = static_cast<double>(za) - static_cast<double>(m);  // exact
-  finish_target_stats(st, mz, dza, sz, ed, ea);
-  if (any_inf) st.H = NAN;
+  finish_target_stats(st, m, dza, sz, ed, ea);
   return st;
 }
 
@@ -196,21 +190,20 @@ __device__ __forceinline__ double behaviour_exp_sum(const In* yr, int act_c, dou
   float y[A_];
   const float my = read_row_max<A_>(yr, y);
   double sy = -0.0;
-  auto terms = [&](const float (&x)[A_], float mx) {
-    const double mxl = static_cast<double>(mx) * kLog2eF64;
+  auto terms = [&](auto careful, float shift) {
+    constexpr bool kCareful = decltype(careful)::value;
+    auto shifted = [&](float x) { return kCareful ? x - shift : x; };
+    const double myl = static_cast<double>(shifted(my)) * kLog2eF64;
     static_for<A_>([&](auto J) {
       constexpr int j = decltype(J)::value;
-      sy += exp2_f64_term<false>(fma(static_cast<double>(x[j]), kLog2eF64, -mxl));
+      sy += exp2_f64_term<kCareful>(fma(static_cast<double>(shifted(y[j])), kLog2eF64, -myl));
       asm volatile("" : "+v"(sy));
     });
   };
-  if (row_plain<A_>(y, my)) {
-    terms(y, my);
-  } else {
-    bool any_inf;
-    const float m = bring_within<A_>(y, my, &any_inf);
-    terms(y, m);
-  }
+  if (__all(row_plain<A_>(y, my)))
+    terms(std::false_type{}, 0.0f);
+  else
+    terms(std::true_type{}, row_shift(my));
   if (!__builtin_isfinite(my)) sy = NAN;
   *dya = static_cast<double>(logit_to_float(yr[act_c])) - static_cast<double>(my);
   return sy;
@@ -219,12 +212,12 @@ __device__ __forceinline__ double behaviour_exp_sum(const In* yr, int act_c, dou
 //
 // zo (precise mode; may be null) receives the target row as float32, for
 // callers that keep it in registers until the gradient.
-template <int A_, bool kPrecise, typename In>
+template <int A_, bool kPrecise, bool kGrad, bool kReread, typename In>
 __device__ __forceinline__ RowStats row_stats(In* zr, const In* yr, int act_c, bool act_ok,
                                               bool beh_lp, bool no_ratio, float lmu, float* e,
                                               float* zo = nullptr) {
   if constexpr (kPrecise) {
-    RowStats st = target_row_stats<A_>(zr, act_c, e, zo);
+    RowStats st = target_row_stats<A_, kGrad, kReread>(zr, act_c, e, zo);
     if (no_ratio) {
       st.ratio = act_ok ? 1.0 : NAN;
     } else if (beh_lp) {
@@ -240,6 +233,7 @@ __device__ __forceinline__ RowStats row_stats(In* zr, const In* yr, int act_c, b
     const float za = logit_to_float(zr[act_c]);
     const float mz = row_max<A_>(zr);
     st.mz = mz;
+    st.za = za;
     float ed = 0.f;  // sum_j e_j (z_j - m_z), for the entropy
     float sz = 0.f, sy = 0.f;
 #pragma unroll

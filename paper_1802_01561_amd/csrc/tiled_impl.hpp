@@ -470,8 +470,8 @@ __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t 
     float e_reg[A_], z_reg[A_];
     float* const lo = kGrad ? reinterpret_cast<float*>(lds_g) + s * S::OUT_PITCH + lane_local * A_ : e_reg;
     float* const e_out = kGrad && !kRowRegs ? lo : e_reg;
-    RowStats st = row_stats<A_, kPrecise>(zr, yr, act_c, act_ok, beh_lp, no_ratio, lmu, e_out,
-                                          kRowRegs ? z_reg : nullptr);
+    RowStats st = row_stats<A_, kPrecise, kGrad, kGrad && !kRowRegs>(zr, yr, act_c, act_ok, beh_lp, no_ratio, lmu,
+                                                                     e_out, kRowRegs ? z_reg : nullptr);
     const StepWeights w = variant_weights(correction, clip_above(st.ratio, rho_bar),
                                           lam * clip_above(st.ratio, c_bar), lam, act_ok);
 
@@ -611,7 +611,7 @@ __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t 
       const float adv32 = static_cast<float>(adv) * pg_w;
       const float beta = st.inv_s * ce;
       const float alpha = st.inv_s * adv32 - beta * K;
-      const float za = logit_to_float(zr[act_c]);
+      const float za = st.za;
       const float out_a = -adv32 * st.one_minus_pa + ce * pa * (za - K);
       if (step_ok) {
         const double log_pa = !act_ok ? NAN : eps_mode ? log_prob_plus_eps<kPrecise>(st, a.epsilon) : st.log_pa;
@@ -762,11 +762,20 @@ __device__ __forceinline__ int64_t first_tile_of_workgroup() {
 // When a batch has a whole multiple of that many tiles, this runs it as one
 // even generation: one workgroup per tile would instead start a second wave of
 // workgroups whenever a slot frees, and leave the chip partly idle at the end.
+// The long-run float32 loss kernels of A = 9 use few enough registers for a third
+// wave per SIMD, and are held to two: their batches are whole generations of two
+// workgroups a CU, which a third slot lets start unevenly (T = 300, B = 32768 227 ->
+// 238 us; three fit the kernels of other types and options from the start).
+template <int A_, typename In, int L, bool kGrad, int kPlain>
+constexpr bool kHoldsTwo = kGrad && L <= 8 && A_ == 9 && std::is_same_v<In, float> &&
+                           (kPlain == kPlainCall || kPlain == kPlainRewards);
+
 // The fp64 ratio mode with A > 18 is asked for two waves per SIMD explicitly:
 // left to itself the compiler gives A = 19 two registers more than fit.
 template <int A_, int LANES, typename In, int L, bool kGrad, bool kPrecise, bool kMulti, int kPlain = kGeneralCall,
           bool kFar = false>
-__global__ __launch_bounds__(LANES* L, (kPrecise && A_ >= 18) ? 2 : 1) void tiled_kernel(
+__global__ __launch_bounds__(LANES* L) __attribute__((amdgpu_waves_per_eu(
+    (kPrecise && A_ >= 18) ? 2 : 1, kHoldsTwo<A_, In, L, kGrad, kPlain> ? 2 : 8))) void tiled_kernel(
     StepArgs a, int64_t tiles_per_wg) {
   using S = Tile<A_, LANES, In, L>;
   constexpr int NT = S::NT;
@@ -1087,17 +1096,23 @@ template <int A_, typename In, typename Sh, typename... Rest>
 bool launch_long_loss(const StepArgs& a, hipStream_t st, int64_t* nwg, hipError_t* err, int cus) {
   if (a.B % Sh::LANES == 0) {
     const int64_t tiles = a.B / Sh::LANES;
-    const int per_cu = is_plain_vtrace(a) ? loss_workgroups_per_cu<A_, Sh::LANES, In, Sh::L, kPlainCall>()
-                       : is_plain_vtrace_any_rewards(a)
-                           ? loss_workgroups_per_cu<A_, Sh::LANES, In, Sh::L, kPlainRewards>()
-                       : is_plain_vtrace_log_probs(a)
-                           ? loss_workgroups_per_cu<A_, Sh::LANES, In, Sh::L, kPlainLogProbs>()
-                           : loss_workgroups_per_cu<A_, Sh::LANES, In, Sh::L, kGeneralCall>();
-    const int64_t resident = static_cast<int64_t>(per_cu) * cus;
-    if (per_cu * (Sh::LANES * Sh::L / kWave) >= kMinWavesPerCu && resident > 0 && tiles % resident == 0 &&
-        tiles <= kMaxGenerations * resident) {
-      *err = launch_shape<A_, Sh::LANES, In, Sh::L, false, true>(a, Mode::LossGrad, st, nwg, false);
-      return true;
+    const int fit = is_plain_vtrace(a) ? loss_workgroups_per_cu<A_, Sh::LANES, In, Sh::L, kPlainCall>()
+                    : is_plain_vtrace_any_rewards(a)
+                        ? loss_workgroups_per_cu<A_, Sh::LANES, In, Sh::L, kPlainRewards>()
+                    : is_plain_vtrace_log_probs(a)
+                        ? loss_workgroups_per_cu<A_, Sh::LANES, In, Sh::L, kPlainLogProbs>()
+                        : loss_workgroups_per_cu<A_, Sh::LANES, In, Sh::L, kGeneralCall>();
+    // Whole generations of the workgroups that are resident, or, of kernels that
+    // three fit, of two a CU (A = 9: log-probabilities or bfloat16, whose batches of
+    // 2^14 to 2^17 lanes took 16-lane tiles otherwise: T = 100, B = 16384, log-
+    // probabilities 60 -> 40 us, bfloat16 61 -> 47; B = 131072, T = 20 174 -> 59).
+    for (int per_cu = fit; per_cu > 0 && per_cu >= (fit < 2 ? fit : 2); --per_cu) {
+      const int64_t resident = static_cast<int64_t>(per_cu) * cus;
+      if (per_cu * (Sh::LANES * Sh::L / kWave) >= kMinWavesPerCu && tiles % resident == 0 &&
+          tiles <= kMaxGenerations * resident) {
+        *err = launch_shape<A_, Sh::LANES, In, Sh::L, false, true>(a, Mode::LossGrad, st, nwg, false);
+        return true;
+      }
     }
   }
   return launch_long_loss<A_, In, Rest...>(a, st, nwg, err, cus);

@@ -65,6 +65,17 @@ def test_variants(T, B, correction, log_probs, transform):
                          reward_transform=transform, grad_bf16=True)
 
 
+@pytest.mark.parametrize("T,B,log_probs,bf16", [(20, 16384, True, False), (17, 32768, False, True),
+                                                (9, 49152, True, True), (5, 65536, False, False)])
+def test_whole_generations_of_two_or_three(T, B, log_probs, bf16):
+    """A = 9 batches that are whole generations of two workgroups a CU, or of the
+    three that fit some of the long-run kernels."""
+    tr = make_random(T, B, 9, 9150 + T, noise_std=1.0, end_prob=0.03, bf16=bf16)
+    log_case(f"long-run tiles T={T} B={B} lp={log_probs} bf16={bf16}")
+    check_io_variant(tr, Params(1.0, 1.0, 1.0), log_probs=log_probs, reward_transform="clip", grad_bf16=bf16,
+                     lanes=[0, 1, 31, 32, B // 2, B // 3, B - 33, B - 1])
+
+
 @pytest.mark.parametrize("T,B,A", [(300, 40, 9), (385, 461, 7)])
 def test_unclipped_weights_and_replays(T, B, A):
     """(inf, inf, 1) through several waves per lane, and the captured call equal
