@@ -120,13 +120,17 @@ __device__ __forceinline__ void finish_target_stats(RowStats& st, float mz, doub
 }
 
 // In a wave with a row that is not plain every row takes the clamped terms (a plain
-// row's are the same bits), of its logits less their shift.  For the gradient such a
-// row's logits are then changed to ones with the same softmax, shifted and with
-// masked ones raised to 1e4 below the maximum, where their exponentials are 0 all the
-// same: in zo or, for a caller that reads the row again (kReread), in place, to go
-// with st.mz and st.za.  (-inf logits make the entropy NaN, and with it the row.)
-template <int A_, bool kGrad, bool kReread, typename In>
-__device__ __forceinline__ RowStats target_row_stats(In* zr, int act_c, float* e, float* zo) {
+// row's are the same bits), of its logits less their shift.  For the gradient
+// row_stats then changes such a row's logits to ones with the same softmax, which go
+// with st.mz: shifted, and with masked ones raised to 1e4 below the maximum, where
+// their exponentials are 0 all the same.  (-inf logits make the entropy NaN, and with
+// it the row.)
+__device__ __forceinline__ float raised_logit(float x, float m, float shift) {
+  return fmaxf(x - shift, (m - shift) - 1e4f);
+}
+
+template <int A_, typename In>
+__device__ __forceinline__ RowStats target_row_stats(const In* zr, int act_c, float* e, float* zo, bool* is_plain) {
   RowStats st;
   const float za = logit_to_float(zr[act_c]);
   float z[A_];
@@ -164,21 +168,8 @@ __device__ __forceinline__ RowStats target_row_stats(In* zr, int act_c, float* e
     const float shift = row_shift(m);
     terms(std::true_type{}, shift);
     m -= shift;
-    if (kGrad && !plain) {
-#pragma unroll
-      for (int j = 0; j < A_; ++j) {
-        const float x = fmaxf(z[j] - shift, m - 1e4f);
-        st.za = j == act_c ? x : st.za;
-        if (zo != nullptr) zo[j] = x;
-        if constexpr (kReread) {
-          if constexpr (std::is_same_v<In, float>)
-            zr[j] = x;
-          else
-            zr[j] = to_bf16(x);
-        }
-      }
-    }
   }
+  *is_plain = plain;
   finish_target_stats(st, m, dza, sz, ed, ea);
   return st;
 }
@@ -212,12 +203,15 @@ __device__ __forceinline__ double behaviour_exp_sum(const In* yr, int act_c, dou
 //
 // zo (precise mode; may be null) receives the target row as float32, for
 // callers that keep it in registers until the gradient.
-template <int A_, bool kPrecise, bool kGrad, bool kReread, typename In>
+// Without zo the caller may read the row again for the gradient (kReread); both are
+// given the logits that go with st.mz.
+template <int A_, bool kPrecise, bool kReread, typename In>
 __device__ __forceinline__ RowStats row_stats(In* zr, const In* yr, int act_c, bool act_ok,
                                               bool beh_lp, bool no_ratio, float lmu, float* e,
                                               float* zo = nullptr) {
   if constexpr (kPrecise) {
-    RowStats st = target_row_stats<A_, kGrad, kReread>(zr, act_c, e, zo);
+    bool plain;
+    RowStats st = target_row_stats<A_>(zr, act_c, e, zo, &plain);
     if (no_ratio) {
       st.ratio = act_ok ? 1.0 : NAN;
     } else if (beh_lp) {
@@ -226,6 +220,24 @@ __device__ __forceinline__ RowStats row_stats(In* zr, const In* yr, int act_c, b
       double dya;
       const double sy = behaviour_exp_sum<A_>(yr, act_c, &dya);
       st.ratio = act_ok ? exp2_f64((st.dza - dya) * kLog2eF64) * (sy * st.inv) : NAN;
+    }
+    // (After the behaviour row: ahead of it the change held its reads back, in bf16 at
+    // T = 20, B = 16384, A = 4 22.3 -> 24.5 us, or cost registers, at A = 17, T = 1000,
+    // B = 32 22.6 -> 32.9.)
+    if ((kReread || zo != nullptr) && !plain) {
+      const float m = row_max<A_>(zr), shift = row_shift(m);
+#pragma unroll
+      for (int j = 0; j < A_; ++j) {
+        const float x = raised_logit(logit_to_float(zr[j]), m, shift);
+        if (zo != nullptr) zo[j] = x;
+        if constexpr (kReread) {
+          if constexpr (std::is_same_v<In, float>)
+            zr[j] = x;
+          else
+            zr[j] = to_bf16(x);
+        }
+        if (j == act_c) st.za = x;
+      }
     }
     return st;
   } else {

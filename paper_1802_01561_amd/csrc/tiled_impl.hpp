@@ -470,8 +470,8 @@ __device__ __forceinline__ void chunk_walk(const StepArgs& a, v4u* lds, int64_t 
     float e_reg[A_], z_reg[A_];
     float* const lo = kGrad ? reinterpret_cast<float*>(lds_g) + s * S::OUT_PITCH + lane_local * A_ : e_reg;
     float* const e_out = kGrad && !kRowRegs ? lo : e_reg;
-    RowStats st = row_stats<A_, kPrecise, kGrad, kGrad && !kRowRegs>(zr, yr, act_c, act_ok, beh_lp, no_ratio, lmu,
-                                                                     e_out, kRowRegs ? z_reg : nullptr);
+    RowStats st = row_stats<A_, kPrecise, kGrad && !kRowRegs>(zr, yr, act_c, act_ok, beh_lp, no_ratio, lmu, e_out,
+                                                              kRowRegs ? z_reg : nullptr);
     const StepWeights w = variant_weights(correction, clip_above(st.ratio, rho_bar),
                                           lam * clip_above(st.ratio, c_bar), lam, act_ok);
 

@@ -53,6 +53,15 @@ def test_shapes(T, B, A, bf16):
         assert_close("targets.pg_advantages", np_out(pg)[:, lanes], o.pg_advantages)
 
 
+# Both sides of the lines between 8, 16 and 32 lanes (on a 256-CU part).
+@pytest.mark.parametrize("T,B,A,bf16", [(125, 4093, 4, False), (100, 4090, 8, False), (100, 4096, 9, False),
+                                        (48, 4096, 18, True), (300, 8200, 10, False), (340, 9001, 9, True),
+                                        (64, 24600, 5, False), (20, 4096, 15, True), (16, 7999, 9, False),
+                                        (9, 16001, 9, False), (17, 8192, 9, False), (130, 15900, 9, False)])
+def test_shapes_of_full_chips(T, B, A, bf16):
+    test_shapes(T, B, A, bf16)
+
+
 @pytest.mark.parametrize("T,B", [(257, 37), (385, 461), (70, 9), (40, 19)])
 @pytest.mark.parametrize("correction,log_probs,transform", [("vtrace", True, "clip"), ("epsilon", False, None),
                                                             ("one_step_is", False, "asymmetric")])
