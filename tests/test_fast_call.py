@@ -125,6 +125,84 @@ def test_same_results_as_the_python_path(dtype, monkeypatch):
         assert (a is None and b is None) or torch.equal(a, b)
 
 
+VARIANTS = [
+    dict(behaviour="log_probs", reward_transform="clip"),
+    dict(grad_dtype=torch.bfloat16, reward_transform="asymmetric"),
+    dict(behaviour="log_probs", grad_dtype=torch.bfloat16, correction="one_step_is", q_estimate="baseline"),
+    dict(correction="epsilon", epsilon=1e-2)]
+SCALARS = dict(rho_bar=1.5, c_bar=0.75, lam=0.9)
+COSTS = dict(baseline_cost=0.7, entropy_cost=0.03)
+
+
+def _both_paths(monkeypatch, calls):
+    """Each call's outputs by the native marshalling (which must take all of them)
+    and by the Python path, in the same buffers."""
+    seen = _count(monkeypatch)
+    results = []
+    for path in ("native", "python"):
+        if path == "python":
+            monkeypatch.setattr(binding, "_fast_call", lambda first: None)
+        got = []
+        for call in calls:
+            out = call()
+            torch.cuda.synchronize()
+            got += [None if t is None else t.clone() for t in out]
+            for t in out:
+                if t is not None:
+                    t.fill_(-7.0)
+        results.append(got)
+    assert seen == {"ran": len(calls), "declined": 0}
+    for i, (a, b) in enumerate(zip(*results)):
+        assert (a is None and b is None) or torch.equal(a, b), i
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("variant", VARIANTS)
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("optional", [False, True])
+def test_variants_as_the_python_path(variant, dtype, optional, monkeypatch):
+    print(f"[case] fast call {variant} {dtype} optional outputs={optional}", flush=True)
+    T, B, A = 20, 7, 9
+    x, out = _loss_args("cuda", T, B, A, dtype)
+    if variant.get("behaviour") == "log_probs":
+        x["behaviour_logits"] = -x["rewards"].abs() - 0.5
+    out = out._replace(d_logits=out.d_logits.to(variant.get("grad_dtype", torch.float32)),
+                       vs=torch.empty_like(x["values"]) if optional else None,
+                       pg_advantages=torch.empty_like(x["values"]) if optional else None,
+                       lane_losses=out.lane_losses if optional else None)
+    ws = vt.Workspace(T, B, A)
+    vs, pg = torch.empty_like(x["values"]), torch.empty_like(x["values"])
+    of_targets = {k: v for k, v in variant.items() if k != "grad_dtype"}
+    _both_paths(monkeypatch, [
+        lambda: vt.vtrace_loss_grad(**x, **SCALARS, **COSTS, **variant, out=out, workspace=ws),
+        lambda: vt.vtrace_targets(**x, **SCALARS, **of_targets, vs=vs, pg_advantages=pg, workspace=ws)])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("variant", [{}, *VARIANTS])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("optional", [False, True])
+def test_output_layer_as_the_python_path(variant, dtype, optional, monkeypatch):
+    print(f"[case] fast call, output layer {variant} {dtype} optional outputs={optional}", flush=True)
+    T, B, A, H = 20, 7, 9, 64
+    x, _ = _loss_args("cuda", T, B, A, dtype)
+    g = torch.Generator().manual_seed(2)
+    f = lambda *s: torch.randn(*s, generator=g).cuda()  # noqa: E731
+    args = dict(hidden=f(T, B, H).tanh().bfloat16(), head_weight=(f(H, A + 1) / 8).bfloat16(), head_bias=f(A + 1),
+                behaviour_logits=x["behaviour_logits"], actions=x["actions"], rewards=x["rewards"],
+                discounts=x["discounts"], bootstrap_value=x["bootstrap_value"])
+    if variant.get("behaviour") == "log_probs":
+        args["behaviour_logits"] = -x["rewards"].abs() - 0.5
+    e = dict(dtype=torch.float32, device="cuda")
+    more = (torch.empty((T, B), **e), torch.empty((T, B), **e), torch.empty((B, 3), **e),
+            torch.empty((T, B, A + 1), **e)) if optional else (None,) * 4
+    out = vt.HeadLossGrad(torch.empty(4, **e), torch.empty((T, B, H), **e).to(variant.get("grad_dtype", torch.float32)),
+                          torch.empty((H, A + 1), **e), torch.empty(A + 1, **e), *more)
+    ws = vt.Workspace(T, B, A, H=H)
+    _both_paths(monkeypatch, [
+        lambda: vt.vtrace_head_loss_grad(**args, **SCALARS, **COSTS, **variant, out=out, workspace=ws)])
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name,change,error", [
     ("actions", lambda t: t.long(), TypeError), ("rewards", lambda t: t.cpu(), ValueError),
