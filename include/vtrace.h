@@ -322,8 +322,15 @@ vtrace_status vtrace_gather_logits(
  *   d_weight        [H,A+1] float32;  d_bias [A+1] float32
  *   vs, pg_advantages, lane_losses   optional, as in vtrace_loss_grad
  *   outputs         optional [T,B,A+1] float32: the layer's outputs o
- *   workspace       required, >= vtrace_head_workspace_bytes(T,B,A,H) bytes,
- *                   16-byte aligned, cleared once by vtrace_workspace_init
+ *   workspace       required, vtrace_head_workspace_bytes(T,B,A,H) bytes, 16-byte
+ *                   aligned, cleared once by vtrace_workspace_init.  That is room
+ *                   for a workgroup per lane, which short batches (T > 16 and up to
+ *                   256 lanes, 512 with T > 32) run on; a smaller one, down to room
+ *                   for a workgroup per four lanes (256 bytes, 24 per workgroup
+ *                   rounded up to 256, and 4 (H + 1) C per workgroup, C = 16 columns
+ *                   or 32 from A = 16 on, at most 512 workgroups), is accepted and
+ *                   gives those the slower split of four lanes a workgroup, whose
+ *                   sums round in another order
  * The products use bfloat16 inputs with float32 accumulation; G enters them as
  * a bfloat16 pair (high part + low part, 2^-17 relative), so d_hidden keeps
  * float32 accuracy.  d_weight, d_bias and the losses are reduced in a fixed

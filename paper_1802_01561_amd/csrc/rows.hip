@@ -13,19 +13,23 @@
 //  2. after the chunk's one barrier every wave reads them with thread i of the
 //     wave on step i, and forms the step's statistics, weights and the reverse
 //     recursion (Remark 1) as one affine scan over the wave.  Each of the four
-//     waves does this for all L steps (about a sixth of a chunk's arithmetic),
-//     which costs less than a second barrier;
+//     waves does this for all L steps, which costs less than a second barrier;
 //  3. each group takes its rows' gradient coefficients from that step's thread
 //     and writes the gradient from registers.
 // The next chunk's rows are loaded before step 2.  LDS is double-buffered, so
 // that a wave may start the next chunk while others still read this one's sums.
 //
-// What bounds it: the float64 exponentials (about 15 instructions per logit)
-// and, for small batches, the chain of T / L chunks.  Measured (loss call, fp32
-// logits, against the generic kernel, whose single thread per lane reads and
-// writes rows uncoalesced): T = 100, B = 512, A = 48 3156 -> 21 us; T = 100,
-// B = 4096, A = 48 3208 -> 132 us (0.08 -> 1.85 TB/s) and A = 22 1395 -> 95 us;
-// T = 20, B = 16384, A = 48 658 -> 176 us.  Three waves per SIMD spill nothing
+// What bounds it: vector instructions, and for small batches the chain of T / L
+// chunks.  Counted at T = 100, B = 4096 (loss call, fp32): 40.5 M wave instructions
+// at A = 48 and 35.3 M at A = 22, which keep the vector ALUs busy for more than half
+// of 117 and 89 us; per 4 rows of 16 threads 308, of which a column of the two rows
+// takes 39 and the rest, three fifths, belongs to the step (the reductions over the
+// group, and statistics and scan once per wave, also of the last chunk's steps
+// before t = 0).  HBM moves the inputs and outputs alone (78.7 MB written, 80.3
+// algorithmic).  Measured (loss call, fp32 logits, against the generic kernel, whose
+// single thread per lane reads and writes rows uncoalesced): T = 100, B = 512, A = 48
+// 3156 -> 21 us; T = 100, B = 4096, A = 48 3208 -> 117 us (0.08 -> 2.1 TB/s) and A = 22
+// 1395 -> 89 us; T = 20, B = 16384, A = 48 658 -> 164 us.  Three waves per SIMD spill nothing
 // at K = 2 (116 -> 95 us at A = 22) but do from K = 3 on, where two are faster
 // (T = 1000, B = 1024, A = 64: 268 against 350 us).
 #include "device_common.hpp"
